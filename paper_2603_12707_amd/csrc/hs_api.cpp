@@ -627,7 +627,7 @@ int hs_model_create(const hs_config *cfg, const hs_weights *w, int32_t max_batch
     if (ns > 1) entries = std::max(entries, (int64_t)nq * nh * ns);
   }
   m->part_entries = entries;
-  m->splitk_floats = (int64_t)SPLITK_MAX * max_batch * std::max(c.d_model, (c.n_heads + 2 * c.n_kv_heads) * c.head_dim);
+  m->splitk_floats = splitk_floats_for(max_batch, rows, std::max(c.d_model, (c.n_heads + 2 * c.n_kv_heads) * c.head_dim));
 
   struct Alloc {
     void **p;
@@ -1032,9 +1032,9 @@ extern "C" int hs_decode_step_static(hs_model *m, hs_kv *kv, const int32_t *toke
   // the step's scratch, carved in 256-byte aligned pieces
   const int64_t b = dtype_bytes(c.dtype), nhd = (int64_t)c.n_heads * c.head_dim;
   const int64_t qkv_rows = (int64_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim;
-  const int64_t splitk_floats = (int64_t)SPLITK_MAX * B * std::max<int64_t>(c.d_model, qkv_rows);
+  int64_t splitk_floats = splitk_floats_for(B, B, std::max<int64_t>(c.d_model, qkv_rows));
   const int64_t entries = ns > 1 ? (int64_t)B * c.n_heads * ns : 1;
-  const uint64_t sizes[10] = {(uint64_t)B * c.d_model * 4,
+  uint64_t sizes[10] = {(uint64_t)B * c.d_model * 4,
                               (uint64_t)(B * nhd * b),
                               (uint64_t)(act_elems(B, nhd) * b),
                               (uint64_t)(act_elems(B, c.ffn_dim) * b),
@@ -1045,6 +1045,16 @@ extern "C" int hs_decode_step_static(hs_model *m, hs_kv *kv, const int32_t *toke
                               (m->w.lm_head && !logits) ? (uint64_t)B * c.vocab * 4 : 0u,
                               0u};
   uint64_t offs[10], total = 0;
+  for (int i = 0; i < 10; ++i) total += (sizes[i] + 255) / 256 * 256;
+  // a step whose whole K-split workspace does not fit takes fewer splits
+  // (never less than the deferred sums of a narrow batch need)
+  const uint64_t least = std::min<uint64_t>(sizes[5], (uint64_t)SPLITK_MAX * B * c.d_model * 4);
+  if (total > HS_STATIC_SCRATCH_BYTES) {
+    const uint64_t over = (total - HS_STATIC_SCRATCH_BYTES + 255) / 256 * 256;
+    sizes[5] = sizes[5] > over + least ? sizes[5] - over : least;
+    splitk_floats = (int64_t)(sizes[5] / 4);
+  }
+  total = 0;
   for (int i = 0; i < 10; ++i) {
     offs[i] = total;
     total += (sizes[i] + 255) / 256 * 256;

@@ -698,13 +698,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
   // lane (c, q) holds rows d = (4 q + i) * 8 + dt of its column's output
   const int64_t orow = roff + my_sq;
   const int ocol = (j * G + sh) * HD;
+  // row i's elements dt = 0..7 are one 16-byte chunk, in either layout of the output
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt)
+  for (int i = 0; i < 4; ++i) {
+    const int d = (4 * lg + i) * 8;
+    float e[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int d = (4 * lg + i) * 8 + dt;
-      if (d < HD) st_elem<DT>(a.out, attn_out_at(a, orow, ocol + d, HD), O[dt][i] / L);
-    }
+    for (int dt = 0; dt < 8; ++dt) e[dt] = O[dt][i] / L;
+    if (d < HD) *(u32x4 *)((uint16_t *)a.out + attn_out_at(a, orow, ocol + d, HD)) = pack<DT>(e);
+  }
 }
 
 // o = sum_s e^(m_s - M) o_s / sum_s e^(m_s - M) l_s over the n_split splits

@@ -69,6 +69,19 @@ __device__ __forceinline__ void st_elem(void *p, int64_t i, float v) {
   else ((uint16_t *)p)[i] = (uint16_t)f32_to_bf16(v);
 }
 
+// two neighbouring elements, i even
+template <int DT>
+__device__ __forceinline__ void st_elem2(void *p, int64_t i, float v0, float v1) {
+  if constexpr (DT == HS_F32) {
+    ((float *)p)[i] = v0;
+    ((float *)p)[i + 1] = v1;
+  } else if constexpr (DT == HS_F16) {
+    *(uint32_t *)((uint16_t *)p + i) = f32_to_f16(v0) | (f32_to_f16(v1) << 16);
+  } else {
+    *(uint32_t *)((uint16_t *)p + i) = f32_to_bf16(v0) | (f32_to_bf16(v1) << 16);
+  }
+}
+
 // 16-byte chunk -> CE floats
 template <int DT>
 __device__ __forceinline__ void unpack(u32x4 w, float *f) {

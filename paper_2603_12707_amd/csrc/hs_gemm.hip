@@ -6,7 +6,7 @@
 // GEMM is organised as one sequential pass over a packed copy of each matrix:
 // a 16-row x 256-byte tile slice is stored as 1 KB in MFMA lane order, so that
 // every wave-wide load instruction reads 1 KB of contiguous HBM.
-#include "hs_device.h"
+#include "hs_gemm_dma.h"
 
 #include <algorithm>
 
@@ -47,228 +47,6 @@ __global__ __launch_bounds__(256) void k_pack(const void *src, void *dst, int64_
     if (row < N && (int64_t)kc * CE < K) v = ld16((const S *)src + row * K + (int64_t)kc * CE);
     *(u32x4 *)((S *)dst + i * CE) = v;
   }
-}
-
-// ---------------------------------------------------------------------------
-// row tiles
-// ---------------------------------------------------------------------------
-// q/k/v: R consecutive tiles of the q, k, v matrices taken in turn (their
-// rows packed in head-paired order); SwiGLU pairs row j of the gate and of
-// the up projection; the other epilogues take R consecutive tiles.
-// rows of a K-split GEMM's partials: the residual rows, or q|k|v rows in turn
-__host__ __device__ inline int split_rows(const GemmArgs &a, int epi) {
-  return epi_qkv(epi) ? (a.n_heads + 2 * a.n_kv) * a.head_dim : a.rows[0];
-}
-
-template <int EPI, int R>
-__device__ __forceinline__ void tile_map(const GemmArgs &a, int g, int *mat, int *row0) {
-  if constexpr (epi_qkv(EPI)) {
-    const int tq = a.n_heads * a.head_dim / 16, tk = a.n_kv * a.head_dim / 16;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      int m = 0, t = g * R + r;
-      if (t >= tq) {
-        t -= tq;
-        m = 1;
-        if (t >= tk) {
-          t -= tk;
-          m = 2;
-        }
-      }
-      mat[r] = m;
-      row0[r] = 16 * t;  // past the v rows for a partial last group
-    }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    mat[0] = 0;
-    mat[1] = 1;
-    row0[0] = row0[1] = 16 * g;
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      mat[r] = 0;
-      row0[r] = 16 * (R * g + r);
-    }
-  }
-}
-
-// PK: the SwiGLU output goes to the packed activation layout where a.out_packed
-// says so (the down projection reads it so, which happens at 2..32 columns,
-// the widths k_gemm serves; the kernels for wider GEMMs never write it)
-template <int DT, int EPI, int R, bool PK = false>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const int *mat, const int *row0, const f32x4 *v,
-                                              int col, int rr) {
-  if constexpr (EPI == EPI_STORE) {
-    float *o = (float *)a.out + (int64_t)col * a.ld_out;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = row0[r] + rr + e;
-        if (row < a.rows[mat[r]]) o[row] = v[r][e];
-      }
-  } else if constexpr (EPI == EPI_RESID) {
-    float *x = a.resid + (int64_t)col * a.ld_resid;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = row0[r] + rr + e;
-        if (row < a.rows[mat[r]]) x[row] += v[r][e];
-      }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    const bool packed = PK && a.out_packed;
-    const int nkb_o = (a.rows[0] / 8 + 15) / 16;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int j = row0[0] + rr + e;
-      if (j < a.rows[0]) {
-        const float g = v[0][e], u = v[1][e];
-        const int64_t at = packed ? packed_x_index(col, j, nkb_o) : (int64_t)col * a.ld_out + j;
-        st_elem<DT>(a.out, at, g / (1.0f + expf(-g)) * u);
-      }
-    }
-  }
-}
-
-// q/k/v epilogue inputs of one thread (one output column, packed rows
-// rr..rr+3 of each of its R tiles: RoPE pairs (j, j + d_h/2) and
-// (j + 1, j + 1 + d_h/2)), read ahead of the main loop: the KV position,
-// capacity and base of the column's request and the RoPE position of each
-// pair first; the cos/sin entries and the biases once those positions are in.
-// Every read goes through a buffer range, so none sits behind a branch.
-template <int R>
-struct QkvIn {
-  int pos, cap, bt;
-  int64_t base;  // start of the block holding pos (negative: none)
-  int p[R][2];
-  float cs[R][2], sn[R][2], b1[R][2], b2[R][2];
-};
-
-template <int DT, int R, bool PAGED>
-__device__ __forceinline__ void qkv_fetch_ids(const GemmArgs &a, const int *mat, const int *row0, int col, int rr,
-                                              bool ok, QkvIn<R> &in) {
-  const bool dec = !a.prefill;
-  const KvRef &kv = a.kv;
-  // decode: column col is request act[col]; prefill: the packed row's request
-  // and its position in that request
-  int req = 0, ppos = 0;
-  if (!dec) {
-    const int i = packed_request(a.pk, col);
-    req = a.pk->req[i];
-    ppos = col - a.pk->cu[i];
-  }
-  const uint32_t nb = (uint32_t)kv.nreq * 4u;
-  if constexpr (PAGED) {
-    const rsrc_t ar = make_rsrc(kv.act, dec ? (uint32_t)a.ncols * 4u : 0u);
-    if (dec) req = (int)bld4(ar, ok ? (uint32_t)col * 4u : BUF_OOB);
-  } else if (dec) {
-    req = col;
-  }
-  const rsrc_t lr = make_rsrc(kv.len, dec ? nb : 0u), cr = make_rsrc(kv.cap, nb);
-  const rsrc_t br = make_rsrc(kv.tab, (uint32_t)kv.ntab * 8u);
-  const rsrc_t pr = make_rsrc(a.rope_pos, dec ? nb : (a.rope_m3 ? 3u * a.rope_ld * 4u : 0u));
-  const uint32_t ro = ok ? (uint32_t)req * 4u : BUF_OOB;
-  const uint32_t pl = bld4(lr, dec ? ro : BUF_OOB);
-  in.cap = (int)bld4(cr, ro);
-  if constexpr (PAGED) {  // the block holding the position
-    const rsrc_t or_ = make_rsrc(kv.toff, nb), tr = make_rsrc(kv.bt, nb);
-    const int toff = (int)bld4(or_, ro);
-    in.bt = max(1, (int)bld4(tr, ro));
-    in.pos = dec ? (int)pl : ppos;
-    const u32x2 bb = bld8(br, ok && in.pos < in.cap ? (uint32_t)(toff + in.pos / in.bt) * 8u : BUF_OOB);
-    in.base = ok && in.pos < in.cap ? (int64_t)(((uint64_t)bb[1] << 32) | bb[0]) : -1;
-  } else {  // one block per request: its start, read beside the length
-    const u32x2 bb = bld8(br, ok ? (uint32_t)req * 8u : BUF_OOB);
-    in.bt = in.cap;
-    in.pos = dec ? (int)pl : ppos;
-    in.base = ok && in.pos < in.cap ? (int64_t)(((uint64_t)bb[1] << 32) | bb[0]) : -1;
-  }
-  const int hd = a.head_dim;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j0 = (row0[r] % hd + rr) >> 1;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int i = j0 + e, sec = i < a.sec0 ? 0 : (i < a.sec1 ? 1 : 2);
-      const bool rot = ok && mat[r] < 2 && (dec || a.rope_m3);
-      const uint32_t pv = bld4(pr, rot ? (uint32_t)(dec ? req : sec * a.rope_ld + col) * 4u : BUF_OOB);
-      in.p[r][e] = (dec || a.rope_m3) ? (int)pv : in.pos;
-    }
-  }
-}
-
-template <int DT, int R>
-__device__ __forceinline__ void qkv_fetch_tab(const GemmArgs &a, const int *mat, const int *row0, int rr, bool ok,
-                                              QkvIn<R> &in) {
-  const int hd = a.head_dim, half = hd >> 1;
-  const rsrc_t tr = make_rsrc(a.rope_tab, (uint32_t)a.rope_max * half * 8u);
-  constexpr int SB = DT == HS_F32 ? 4 : 2;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int m = mat[r], head = row0[r] / hd, j0 = (row0[r] - head * hd + rr) >> 1;
-    const bool live = ok && row0[r] < a.rows[m];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int p = min(max(in.p[r][e], 0), a.rope_max - 1);
-      const u32x2 t = bld8(tr, live && m < 2 ? (uint32_t)(p * half + j0 + e) * 8u : BUF_OOB);
-      in.cs[r][e] = __uint_as_float(t[0]);
-      in.sn[r][e] = __uint_as_float(t[1]);
-    }
-    const rsrc_t bq = make_rsrc(a.bias[m], a.bias[m] ? (uint32_t)a.rows[m] * SB : 0u);
-    const uint32_t o1 = (uint32_t)(head * hd + j0) * SB, o2 = (uint32_t)(head * hd + half + j0) * SB;
-    if constexpr (DT == HS_F32) {
-      const u32x2 v1 = bld8(bq, live ? o1 : BUF_OOB), v2 = bld8(bq, live ? o2 : BUF_OOB);
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        in.b1[r][e] = __uint_as_float(v1[e]);
-        in.b2[r][e] = __uint_as_float(v2[e]);
-      }
-    } else {
-      const uint32_t v1 = bld4(bq, live ? o1 : BUF_OOB), v2 = bld4(bq, live ? o2 : BUF_OOB);
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const uint32_t h1 = (v1 >> (16 * e)) & 0xFFFFu, h2 = (v2 >> (16 * e)) & 0xFFFFu;
-        in.b1[r][e] = DT == HS_F16 ? f16_to_f32(h1) : bf16_to_f32(h1);
-        in.b2[r][e] = DT == HS_F16 ? f16_to_f32(h2) : bf16_to_f32(h2);
-      }
-    }
-  }
-}
-
-// bias, RoPE on q and k, then R(q) to the q workspace and k, v rows appended
-// to the cache at the request's position
-template <int DT, int R, bool PAGED>
-__device__ __forceinline__ void qkv_store(const GemmArgs &a, const int *mat, const int *row0, const f32x4 *v, int col,
-                                          int rr, const QkvIn<R> &in) {
-  constexpr int B = DT == HS_F32 ? 4 : 2;
-  const int hd = a.head_dim, half = hd >> 1;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int m = mat[r];
-    if (row0[r] >= a.rows[m]) continue;
-    const int head = row0[r] / hd, j0 = (row0[r] - head * hd + rr) >> 1;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int i = j0 + e;  // frequency pair, < d_h / 2
-      const float v1 = v[r][2 * e] + in.b1[r][e], v2 = v[r][2 * e + 1] + in.b2[r][e];
-      float o1 = v1, o2 = v2;
-      if (m < 2) {
-        o1 = v1 * in.cs[r][e] - v2 * in.sn[r][e];
-        o2 = v2 * in.cs[r][e] + v1 * in.sn[r][e];
-      }
-      if (m == 0) {
-        void *q = (char *)a.out + ((int64_t)col * a.ld_out + head * hd) * B;
-        st_elem<DT>(q, i, o1);
-        st_elem<DT>(q, i + half, o2);
-      } else if (in.base >= 0) {
-        const int pin = PAGED ? in.pos % in.bt : in.pos;  // position within its block
-        const int64_t off = in.base + ((int64_t)((a.layer * 2 + (m == 2 ? 1 : 0)) * a.n_kv + head) * in.bt + pin) * hd;
-        st_elem<DT>(a.kv.buf, off + i, o1);
-        st_elem<DT>(a.kv.buf, off + i + half, o2);
-      }
-    }
-  }
-
 }
 
 // fp64 sum over the 64 lanes of a wave; every lane gets it.
@@ -353,12 +131,19 @@ __global__ __launch_bounds__(256) void k_rmsnorm(float *x, const void *gain, flo
                                                 const double *pend, int ncols) {
   constexpr int NV = 4;  // 16-byte chunks per thread held in registers
   constexpr int SB = DT == HS_F32 ? 4 : 2;
-  float *xr = x + (int64_t)blockIdx.x * K;
+  // a packed column tile's 16 rows go to one XCD (work groups are dealt to the
+  // 8 of them round robin), whose L2 joins the 16 bytes each row has of every 256
+  int row = blockIdx.x;
+  if (packed && ncols > 32) {
+    row = ((row >> 7) * 8 + (row & 7)) * 16 + ((row >> 3) & 15);
+    if (row >= ncols) return;
+  }
+  float *xr = x + (int64_t)row * K;
   const rsrc_t xq = make_rsrc(xr, (uint32_t)K * 4u);
   const rsrc_t gr = make_rsrc(gain, (uint32_t)K * SB);
   rsrc_t pq[PS > 0 ? PS : 1];
 #pragma unroll
-  for (int s = 0; s < PS; ++s) pq[s] = make_rsrc(pend + ((int64_t)s * ncols + blockIdx.x) * K, (uint32_t)K * 8u);
+  for (int s = 0; s < PS; ++s) pq[s] = make_rsrc(pend + ((int64_t)s * ncols + row) * K, (uint32_t)K * 8u);
   // partials of elements k..k+3: two 16-byte loads per split
   using P4 = u32x4[2];
   auto pend4 = [&](int k, bool ok, P4 (&p)[PS > 0 ? PS : 1]) {
@@ -408,7 +193,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm(float *x, const void *gain, flo
   const float rs = (float)(1.0 / sqrt(block_sum<4>(ss, s_part) / (double)K + (double)eps));
   const int nkb = (K / 8 + 15) / 16;
   // (packed: the 4 elements stay consecutive, k being a multiple of 4)
-  auto at = [&](int k) { return packed ? packed_x_index((int)blockIdx.x, k, nkb) : (int64_t)blockIdx.x * K + k; };
+  auto at = [&](int k) { return packed ? packed_x_index(row, k, nkb) : (int64_t)row * K + k; };
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int k = (u * 256 + (int)threadIdx.x) * 4;
@@ -1240,198 +1025,6 @@ __global__ __launch_bounds__(256) void k_resid_pending(const double *part, int k
 }
 
 // ---------------------------------------------------------------------------
-// weight-stationary GEMM for a few hundred columns
-// ---------------------------------------------------------------------------
-// At 129..256 columns (decode at a large batch) every weight row meets all
-// columns, so a wave that owns WS_RT row tiles of a work unit takes their
-// weights straight from memory into registers (a ring WS_DEPTH stages deep,
-// non-temporal loads) and never shares them: only the activations go through
-// LDS.  A work group = WS_NWC consumer waves (one task of WS_RT row tiles x
-// WS_CT column tiles each) + WS_NP producer waves that stage the activations
-// of each 64-element K stage into a double buffer.  Consumers read each
-// activation sub-block from LDS a few ahead of its MFMAs (scheduling groups
-// keep the reads WS_PF operands ahead) and meet the producers at one barrier
-// per stage.  The grid is one work group per CU looping over work units
-// (row-task group, column group); the column groups of one row group land on
-// the same XCD, where the later ones read the weights from L2.  Taken for the
-// tall matrices that need no K split, gate/up and the LM head: at the
-// batch-256 Qwen-shaped layer gate/up takes 100-107 us against 146 for the
-// LDS-staged kernel.  The short ones (q/k/v, O, down) measured slower here
-// even split into 4-8 K ranges (O 47-55 us against 33, down 89 against 73):
-// each wave waits for its own weights once per stage, so with few work units
-// the latency of the weight stream is exposed.
-// Five consumers: the Qwen-shaped gate/up at batch 256 is 240 work units on
-// 256 CUs (six made 208 units, leaving 48 CUs idle: 103.7 against 95.5 us).
-// A ring three stages deep spills at two waves per SIMD.
-constexpr int WS_RT = 4, WS_CT = 8, WS_NWC = 5, WS_NP = 2, WS_DEPTH = 2, WS_PF = 3, WS_GRID = 256;
-constexpr int WS_MIN_COLS = 129, WS_MAX_COLS = 256;
-
-// one work-group barrier once this wave's LDS accesses are complete; the
-// global loads in flight (the weight ring) are not waited for
-__device__ __forceinline__ void ws_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// row tile r of task t -> matrix and first row (SwiGLU: WS_RT/2 gate tiles,
-// then the matching up tiles)
-template <int EPI>
-__device__ __forceinline__ void ws_tile(int t, int r, int &m, int &r0) {
-  if constexpr (EPI == EPI_SWIGLU) {
-    constexpr int H = WS_RT / 2;
-    m = r < H ? 0 : 1;
-    r0 = 16 * (t * H + r % H);
-  } else {
-    m = 0;
-    r0 = 16 * (t * WS_RT + r);
-  }
-}
-
-template <int DT, int EPI>
-__global__ __launch_bounds__(64 * (WS_NWC + WS_NP)) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_gemm_ws(GemmArgs a) {
-  using S = typename Ty<DT>::S;
-  constexpr int CE = Ty<DT>::CE;
-  constexpr int SB = (int)sizeof(S);
-  constexpr int RT = WS_RT, CT = WS_CT, NWC = WS_NWC, NP = WS_NP, DEPTH = WS_DEPTH, PF = WS_PF;
-  constexpr int XE = 2 * CT, XPT = XE / NP, NB = 2 * CT;
-  constexpr int UNR = DEPTH % 2 == 0 ? DEPTH : 2 * DEPTH;  // stages per unrolled round
-  static_assert(XE % NP == 0 && PF <= NB, "stage split");
-  static_assert(EPI == EPI_SWIGLU || EPI == EPI_STORE, "tall matrices without a K split");
-  __shared__ __align__(16) u32x4 s_x[2][XE * 64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int li = lane & 15, lq = lane >> 4;
-  const int K = a.K, kchunks = K / CE, nkb = (kchunks + 15) >> 4, nsb = nkb * 4;
-  const int per_task = EPI == EPI_SWIGLU ? RT / 2 : RT;
-  const int n_task = ((a.rows[0] + 15) / 16 + per_task - 1) / per_task;
-  const int n_rg = (n_task + NWC - 1) / NWC, n_rg8 = (n_rg + 7) / 8 * 8;
-  const int n_cg = (a.ncols + 16 * CT - 1) / (16 * CT);
-  const int n_units = n_rg8 * n_cg;
-  const rsrc_t xres = make_rsrc(a.x, (uint32_t)a.ncols * K * SB);
-  const int g_begin = 0, g_end = nsb, nstage = (nsb + 1) / 2;
-  for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
-    // unit = ((row group / 8) * n_cg + column group) * 8 + row group % 8
-    const int lo = unit & 7, v = unit >> 3;
-    const int cg = v % n_cg, rg = (v / n_cg) * 8 + lo;
-    if (rg >= n_rg) continue;
-    const int cnt = min(NWC, n_task - rg * NWC);
-    const int colg0 = cg * CT * 16;
-    if (wave >= NWC) {
-      // producer: activation sub-block e = sub * CT + column tile of each stage
-      const int pw = wave - NWC;
-      u32x4 xr[XPT];
-      auto xload = [&](int st) {
-#pragma unroll
-        for (int i = 0; i < XPT; ++i) {
-          const int e = pw + NP * i, sub = e / CT, ct = e % CT, g = g_begin + st * 2 + sub;
-          const int col = colg0 + ct * 16 + li, kc = g * 4 + lq;
-          xr[i] = bld16(xres, g < g_end && col < a.ncols && kc < kchunks ? (uint32_t)(col * K + kc * CE) * SB : BUF_OOB);
-        }
-      };
-      auto xstore = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < XPT; ++i) s_x[buf][(pw + NP * i) * 64 + lane] = xr[i];
-      };
-      xload(0);
-      xstore(0);
-      xload(1);
-      for (int st0 = 0; st0 < nstage; st0 += 2) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (st0 + h < nstage) {
-            ws_barrier();
-            xstore(h ^ 1);
-            xload(st0 + h + 2);
-          }
-        }
-      }
-      ws_barrier();
-    } else if (wave < cnt) {
-      const int task = rg * NWC + wave;
-      int mat[RT], row0[RT];
-      rsrc_t wres[RT];
-#pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        ws_tile<EPI>(task, r, mat[r], row0[r]);
-        wres[r] = make_rsrc((const S *)a.w[mat[r]] + (int64_t)(row0[r] >> 4) * nkb * 256 * CE,
-                            row0[r] < a.rows[mat[r]] ? (uint32_t)nkb * 4096u : 0u);
-      }
-      u32x4 wq[DEPTH][2][RT];
-      auto wload = [&](int slot, int st) {
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          const int g = g_begin + st * 2 + sub;
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-            wq[slot][sub][r] = bld16_stream(wres[r], g < g_end ? (uint32_t)g * 1024u + (uint32_t)lane * 16u : BUF_OOB);
-        }
-      };
-      f32x4 acc[RT][CT];
-#pragma unroll
-      for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < DEPTH; ++s) wload(s, s);
-      auto stage = [&](int st, int slot, int buf) {
-        ws_barrier();
-        u32x4 bq[PF];
-#pragma unroll
-        for (int j = 0; j < PF; ++j) bq[j] = s_x[buf][j * 64 + lane];
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          const u32x4 b = bq[j % PF];
-          if (j + PF < NB) bq[j % PF] = s_x[buf][(j + PF) * 64 + lane];
-          const int sub = j / CT, c = j % CT;
-#pragma unroll
-          for (int r = 0; r < RT; ++r) acc[r][c] = mma<DT>(wq[slot][sub][r], b, acc[r][c]);
-        }
-        // PF operand reads ahead, then RT MFMAs and one read per operand
-        __builtin_amdgcn_sched_group_barrier(0x100, PF, 0);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          __builtin_amdgcn_sched_group_barrier(0x008, RT, 0);
-          if (j + PF < NB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        wload(slot, st + DEPTH);
-      };
-      // whole rounds of UNR stages with no guard, so that the waits for the
-      // weight ring count its loads exactly; then the remaining stages
-      int st0 = 0;
-      for (; st0 + UNR <= nstage; st0 += UNR) {
-#pragma unroll
-        for (int h = 0; h < UNR; ++h) stage(st0 + h, h % DEPTH, h & 1);
-      }
-#pragma unroll
-      for (int h = 0; h < UNR; ++h)
-        if (st0 + h < nstage) stage(st0 + h, h % DEPTH, h & 1);
-      ws_barrier();
-
-      const int rr = 4 * lq;
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        const int col = colg0 + c * 16 + li;
-        if (col >= a.ncols) continue;
-        if constexpr (EPI == EPI_SWIGLU) {
-          constexpr int H = RT / 2;
-#pragma unroll
-          for (int r = 0; r < H; ++r) {
-            const int m2[2] = {0, 1}, r2[2] = {row0[r], row0[r + H]};
-            const f32x4 v2[2] = {acc[r][c], acc[r + H][c]};
-            gemm_epilogue<DT, EPI_SWIGLU, 2>(a, m2, r2, v2, col, rr);
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < RT; ++r) gemm_epilogue<DT, EPI, 1>(a, &mat[r], &row0[r], &acc[r][c], col, rr);
-        }
-      }
-    } else {
-      // no task in this unit: the same barriers
-      for (int st = 0; st < nstage; ++st) ws_barrier();
-      ws_barrier();
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // launch shapes
 // ---------------------------------------------------------------------------
 constexpr int XS_MAX_BYTES = 32 * 1024;  // LDS for normalised activations
@@ -1442,26 +1035,16 @@ hipError_t gemm_launch(const GemmArgs &a, int n_groups, size_t shmem, hipStream_
   g.n_groups = n_groups;
   g.n_colg = (a.ncols + 16 * NT - 1) / (16 * NT);
   const int blocks = g.n_colg > 1 ? (n_groups + 7) / 8 * 8 * g.n_colg : n_groups;
-  // the packed layouts get instantiations of their own, so the usual
-  // row-major loads and stores carry no branch
-  if constexpr (DT != HS_F32) {
-    if constexpr (EPI == EPI_SWIGLU)
-      if (a.out_packed) {
-        if constexpr (XS == 0)
-          if (a.x_packed) {
-            HS_LAUNCH((k_gemm<DT, R, NT, NW, U, PRO, XS, EPI, true, true>), dim3(blocks), dim3(64 * NW), shmem, st, g);
-            return hipGetLastError();
-          }
-        HS_LAUNCH((k_gemm<DT, R, NT, NW, U, PRO, XS, EPI, true, false>), dim3(blocks), dim3(64 * NW), shmem, st, g);
-        return hipGetLastError();
-      }
-    if constexpr (XS == 0)
-      if (a.x_packed) {
-        HS_LAUNCH((k_gemm<DT, R, NT, NW, U, PRO, XS, EPI, false, true>), dim3(blocks), dim3(64 * NW), shmem, st, g);
-        return hipGetLastError();
-      }
-  }
-  HS_LAUNCH((k_gemm<DT, R, NT, NW, U, PRO, XS, EPI, false, false>), dim3(blocks), dim3(64 * NW), shmem, st, g);
+  // the packed layouts get instantiations of their own, so the row-major
+  // stores carry no branch; 16-bit activations read from memory are packed
+  constexpr bool XP = XS == 0 && DT != HS_F32;
+  if (XP != (a.x_packed != 0)) return hipErrorInvalidValue;
+  if constexpr (DT != HS_F32 && EPI == EPI_SWIGLU)
+    if (a.out_packed) {
+      HS_LAUNCH((k_gemm<DT, R, NT, NW, U, PRO, XS, EPI, true, XP>), dim3(blocks), dim3(64 * NW), shmem, st, g);
+      return hipGetLastError();
+    }
+  HS_LAUNCH((k_gemm<DT, R, NT, NW, U, PRO, XS, EPI, false, XP>), dim3(blocks), dim3(64 * NW), shmem, st, g);
   return hipGetLastError();
 }
 
@@ -1550,12 +1133,6 @@ hipError_t gemm_lds_launch(const GemmArgs &a, int tiles16, int k_split, hipStrea
   return split_finish<DT, EPI>(g, st);
 }
 
-template <int DT, int EPI>
-hipError_t gemm_ws_launch(const GemmArgs &a, hipStream_t st) {
-  HS_LAUNCH((k_gemm_ws<DT, EPI>), dim3(WS_GRID), dim3(64 * (WS_NWC + WS_NP)), 0, st, a);
-  return hipGetLastError();
-}
-
 // Many columns.  Where the work-group tile of 16 x 8 row x column tiles (wave
 // tiles of 4 x 4, half the LDS reads per MFMA) still gives LDS_BIG_GROUPS
 // work groups, it is taken (prefill gate/up at 640 rows: 159 against 191 us;
@@ -1574,8 +1151,6 @@ hipError_t gemm_ws_launch(const GemmArgs &a, hipStream_t st) {
 constexpr int LDS_MIN_GROUPS = 72, LDS_BIG_GROUPS = 200, SPLITK_BELOW = 128, SPLITK_TARGET = 256, WIDE_COLS = 2048;
 template <int DT, int EPI>
 hipError_t gemm_tiled(const GemmArgs &p, int tiles16, hipStream_t st) {
-  if constexpr (DT != HS_F32 && (EPI == EPI_SWIGLU || EPI == EPI_STORE))
-    if (p.ncols >= WS_MIN_COLS && p.ncols <= WS_MAX_COLS) return gemm_ws_launch<DT, EPI>(p, st);
   int ng, nc;
   if (p.ncols >= WIDE_COLS && lds_groups<EPI, 16, 16>(p, tiles16, 1, ng, nc) >= LDS_BIG_GROUPS)
     return gemm_lds_launch<DT, EPI, 16, 16>(p, tiles16, 1, st);
@@ -1644,11 +1219,12 @@ hipError_t gemm_shape(const GemmArgs &a, hipStream_t st) {
     // them through MFMA-operand loads)
     p.x_packed = gemm_x_packed(DT, a.ncols, a.K) ? 1 : 0;
     float *x = (float *)a.x;  // rewritten with the pending partials added
+    const int groups = p.x_packed && a.ncols > 32 ? (a.ncols + 127) / 128 * 128 : a.ncols;
     if (a.pend_s == 0)
-      HS_LAUNCH((k_rmsnorm<DT, 0>), dim3(a.ncols), dim3(256), 0, st, x, a.gain, a.eps, a.K, a.h_work, p.x_packed,
+      HS_LAUNCH((k_rmsnorm<DT, 0>), dim3(groups), dim3(256), 0, st, x, a.gain, a.eps, a.K, a.h_work, p.x_packed,
                 nullptr, a.ncols);
     else if (a.pend_s == DEFER_SPLITS && a.pend)
-      HS_LAUNCH((k_rmsnorm<DT, DEFER_SPLITS>), dim3(a.ncols), dim3(256), 0, st, x, a.gain, a.eps, a.K, a.h_work,
+      HS_LAUNCH((k_rmsnorm<DT, DEFER_SPLITS>), dim3(groups), dim3(256), 0, st, x, a.gain, a.eps, a.K, a.h_work,
                 p.x_packed, a.pend, a.ncols);
     else
       return hipErrorInvalidValue;
@@ -1658,7 +1234,15 @@ hipError_t gemm_shape(const GemmArgs &a, hipStream_t st) {
   }
   if (tiles <= 1) return gemm_global_r<DT, EPI, 1>(p, tiles16, st);
   if (tiles <= 2) return gemm_global_r<DT, EPI, 2>(p, tiles16, st);
-  return gemm_tiled<DT, EPI>(p, tiles16, st);
+  if constexpr (DT == HS_F32) {
+    return gemm_tiled<DT, EPI>(p, tiles16, st);
+  } else {
+    int parts = 0;
+    const hipError_t e = gemm_dma<DT>(EPI, p, tiles16, &parts, st);
+    if (e != hipSuccess || !parts) return e;
+    p.k_split = parts;
+    return split_finish<DT, EPI>(p, st);
+  }
 }
 
 // the combine prologue: one column tile whose activations fit the LDS copy
@@ -1684,11 +1268,11 @@ hipError_t gemm_dt(int pro, int epi, const GemmArgs &a, hipStream_t st) {
 
 bool gemm_x_packed(int dtype, int ncols, int K) {
   // the launch shape's choice: activations staged in LDS (one column tile
-  // that fits the copy), from memory (two column tiles at most), or the
-  // tiled kernels
+  // that fits the copy), or read from memory in the packed layout, by k_gemm
+  // (two column tiles at most) or k_gemm_dma
   if (dtype == HS_F32 || ncols <= 0) return false;
   const int tiles = (ncols + 15) / 16;
-  return tiles <= 2 && !(tiles <= 1 && (size_t)ncols * K * 2 <= XS_MAX_BYTES);
+  return !(tiles <= 1 && (size_t)ncols * K * 2 <= XS_MAX_BYTES);
 }
 
 int resid_defer_splits(int dtype, int ncols, int K, int d_model, int64_t cap) {
@@ -1696,8 +1280,8 @@ int resid_defer_splits(int dtype, int ncols, int K, int d_model, int64_t cap) {
   // columns), the next normalisation runs in k_rmsnorm (its columns do not
   // fit the prologue's LDS copy), every split holds a k-block, whole float4
   // rows, and the fp64 partials fit the workspace
-  if (!gemm_x_packed(dtype, ncols, K)) return 0;
   const int tiles = (ncols + 15) / 16;
+  if (!gemm_x_packed(dtype, ncols, K) || tiles > 2) return 0;
   if (tiles <= 1 && (size_t)ncols * d_model * 2 <= XS_MAX_BYTES) return 0;
   if ((K / 8 + 15) / 16 < DEFER_SPLITS || d_model % 4) return 0;
   if (2 * (int64_t)DEFER_SPLITS * ncols * d_model > cap) return 0;
@@ -1711,7 +1295,9 @@ hipError_t launch_resid_pending(const double *part, int k_split, int ncols, int 
   return hipGetLastError();
 }
 
-int64_t act_elems(int64_t rows, int64_t K) { return std::max(rows * K, (int64_t)32 * ((K + 127) / 128 * 128)); }
+int64_t act_elems(int64_t rows, int64_t K) {
+  return (std::max<int64_t>(rows, 32) + 15) / 16 * 16 * ((K + 127) / 128 * 128);
+}
 
 hipError_t launch_gemm(int dtype, int pro, int epi, const GemmArgs &a, hipStream_t st) {
   if (a.ncols <= 0 || a.rows[0] <= 0) return hipSuccess;

@@ -1,0 +1,415 @@
+// hs_gemm_dma.h — GEMM over more than 32 columns in 16-bit storage (large
+// decode batches, prefill rows), both operands copied from memory straight
+// into LDS.
+#pragma once
+
+#include "hs_gemm_epi.h"
+
+#include <type_traits>
+#include <utility>
+
+namespace hs {
+namespace dev {
+
+// Y[c][n] = sum_k X[c][k] W[n][k].  Weights and activations sit in the packed
+// layout (16 rows or columns x 32 elements = 1 KB in MFMA operand order), so
+// one wave-wide 16-byte buffer load to LDS moves one sub-block, lane l's 16
+// bytes to LDS byte 16 l, and a wave reads an MFMA operand back with one
+// conflict-free ds_read_b128.  No register and no write instruction stages the
+// data.
+//
+// A work group of WR x WC waves owns TR = WR RTW row tiles and TC = WC CTW
+// column tiles; wave (wr, wc) computes RTW x CTW of them over the work group's
+// K range.  K advances in stages of one sub-block through a ring of ST stages
+// in LDS.  At stage s a wave waits for its own loads of stage s + 1 (the
+// counter then still covers ST - 2 stages), meets the others at one barrier,
+// requests stage s + ST into the slot that stage s leaves (its operands are in
+// registers since the stage before), reads the operands of stage s + 1, and
+// issues the MFMAs of stage s, the reads spread between them.
+//
+// What bounds it.  Per CU about 38-40 B/ns of operand loads pass (weights from
+// HBM and activations from L2 together, whatever the ring depth from 4 to 18
+// stages), so a tile's time is its bytes, 1 KB x (TR + TC) per stage, and the
+// launcher takes the shape with the fewest bytes per CU that still fills the
+// chip.  At the largest tile (16 x 16) that is as long as the power limit
+// leaves the matrix cores (1.9 GHz, MFMA 65 % busy): 37888 x 3584 over 14400
+// columns runs 2.81-3.06 ms, 1250-1390 TFLOP/s; with both operands staged
+// through registers it took 4.05 ms.  A 4-wave variant with wave tiles of
+// 8 x 8 (one wave per SIMD, a quarter fewer LDS reads) took 3.82 ms.
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+
+__device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  // no destination registers: the data goes to LDS [m0 + 16 lane]
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
+               "s"(rsrc), "s"(soff));
+}
+// at most N of this wave's loads still in flight, its LDS reads done, then a
+// work-group barrier
+template <int N>
+__device__ __forceinline__ void dma_sync() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+// NR LDS reads spread over NM MFMAs
+template <int I, int NR, int NM>
+__device__ __forceinline__ void dma_sched() {
+  if constexpr (I < NR) {
+    __builtin_amdgcn_sched_group_barrier(0x008, NM * (I + 1) / (NR + 1) - NM * I / (NR + 1), 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    dma_sched<I + 1, NR, NM>();
+  } else {
+    __builtin_amdgcn_sched_group_barrier(0x008, NM - NM * NR / (NR + 1), 0);
+  }
+}
+
+// f(0, 1, ...) with the numbers as types
+template <class F, int... T>
+__device__ __forceinline__ void dma_each(F f, std::integer_sequence<int, T...>) {
+  f(std::integral_constant<int, T>{}...);
+}
+
+// four consecutive values in the storage dtype, 8 bytes
+template <int DT>
+__device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d) {
+  if constexpr (DT == HS_F16)
+    return u32x2{f32_to_f16(a) | (f32_to_f16(b) << 16), f32_to_f16(c) | (f32_to_f16(d) << 16)};
+  else
+    return u32x2{f32_to_bf16(a) | (f32_to_bf16(b) << 16), f32_to_bf16(c) | (f32_to_bf16(d) << 16)};
+}
+
+// EPI: EPI_SWIGLU; EPI_QKV (bias, RoPE, R(q), K/V append; K not split); or
+// EPI_STORE, fp32 rows by a.f32_out: logits, K-split partials (residual rows,
+// or q|k|v rows in turn), or the residual add
+template <int DT, int WR, int WC, int RTW, int CTW, int ST, int EPI>
+__global__ __launch_bounds__(64 * WR * WC) __attribute__((amdgpu_waves_per_eu(WR * WC / 4, 2)))
+void k_gemm_dma(GemmArgs a) {
+  constexpr int NW = WR * WC, TR = WR * RTW, TC = WC * CTW;
+  constexpr int NB = TR + TC;               // sub-blocks per stage
+  constexpr int LPW = (NB + NW - 1) / NW;   // of them moved per wave
+  constexpr bool PAD = LPW * NW > NB;       // some waves move an empty one (their counters agree)
+  static_assert(ST % 2 == 0 && (ST - 1) * LPW <= 63, "ring depth");
+  static_assert(EPI != EPI_SWIGLU || RTW % 2 == 0, "gate/up pairs per wave");
+  __shared__ __align__(1024) unsigned char s_mem[(ST * NB + (PAD ? 1 : 0)) * 1024];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave / WC, wc = wave % WC, li = lane & 15, lq = lane >> 4;
+  const int nsb = (a.K / 8 + 15) / 16 * 4;  // sub-blocks of a packed row or column tile
+
+  // Work units in the order (K split, super row of SH row groups, column
+  // group, row group): each XCD (work groups are dealt to the 8 of them round
+  // robin) takes one run of them, so that the units it runs at a time share
+  // their weights and activations in its L2.
+  constexpr int SH = 8;
+  const int nrg = a.n_groups, ncg = a.n_colg, per = nrg * ncg, total = per * a.k_split;
+  const int q8 = total >> 3, r8 = total & 7, xcd = (int)blockIdx.x & 7;
+  const int unit = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + ((int)blockIdx.x >> 3);
+  const int sp = unit / per, u0 = unit - sp * per;
+  const int sr = u0 / (SH * ncg), sh = min(SH, nrg - sr * SH), u1 = u0 - sr * SH * ncg;
+  const int rg = sr * SH + u1 % sh, cg = u1 / sh;
+  // this split's stages [g0, g0 + n): whole k-blocks of 4, at least ST (the launcher sees to it)
+  const int kper = (nsb / 4 + a.k_split - 1) / a.k_split * 4;
+  const int g0 = sp * kper, n = min(nsb, g0 + kper) - g0;
+
+  // row tile t of the work group -> matrix and first row
+  auto tile_of = [&](int t, int &m, int &r0) {
+    if constexpr (EPI == EPI_SWIGLU) {
+      constexpr int H = RTW / 2;
+      const int w = t / RTW, k = t % RTW;
+      m = k < H ? 0 : 1;
+      r0 = 16 * (rg * (TR / 2) + w * H + k % H);
+    } else {
+      int u = rg * TR + t;
+      m = 0;
+      if (a.rows[1] > 0) {  // q, k, v in turn
+        const int tq = a.rows[0] / 16, tk = a.rows[1] / 16;
+        if (u >= tq) {
+          u -= tq;
+          m = 1;
+          if (u >= tk) {
+            u -= tk;
+            m = 2;
+          }
+        }
+      }
+      r0 = 16 * u;  // past the rows in a partial last group
+    }
+  };
+
+  // this wave's LPW sub-blocks of every stage: row tiles first, then column
+  // tiles; tiles past the data have an empty range (nothing is read, and what
+  // their operands hold reaches only outputs that are not stored)
+  u32x4 rs[LPW];
+  uint32_t live[LPW];
+  const int n_ct = (a.ncols + 15) >> 4;
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int b = wave * LPW + i;
+    uint64_t p;
+    bool in;
+    if (b < TR) {
+      int m, r0;
+      tile_of(b, m, r0);
+      in = r0 < a.rows[m];
+      p = (uint64_t)a.w[m] + ((uint64_t)(in ? r0 >> 4 : 0) * nsb + g0) * 1024u;
+    } else {
+      const int ct = cg * TC + b - TR;
+      in = b < NB && ct < n_ct;
+      p = (uint64_t)a.x + ((uint64_t)(in ? ct : 0) * nsb + g0) * 1024u;
+    }
+    rs[i] = u32x4{(uint32_t)p, (uint32_t)(p >> 32), in ? (uint32_t)n * 1024u : 0u, (uint32_t)BUF_WORD3};
+    live[i] = in ? ~0u : 0u;
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)s_mem;
+  const uint32_t vo = (uint32_t)lane * 16u;
+  // With one column group each work group starts its K range at another stage
+  // (wrapping round), so that the chip's row tiles do not walk the same
+  // address bits in step: 37888 x 3584 over 256 columns 84 -> 76 us, 4096 x
+  // 11008 in 8 splits over 64 columns 20.4 -> 18.5 us.  With several column
+  // groups the stages stay in step for the L2.
+  const int rot = ncg == 1 ? (int)(((uint32_t)unit * 37u) % (uint32_t)n) : 0;
+  auto issue = [&](int s, int slot) {
+    int g = s + rot;
+    g -= g >= n ? n : 0;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const int b = wave * LPW + i;
+      const uint32_t dst = PAD && b >= NB ? (uint32_t)(ST * NB) : (uint32_t)(slot * NB + b);
+      dma_1k(rs[i], vo, (uint32_t)g * 1024u & live[i], lds0 + dst * 1024u);
+    }
+  };
+
+  f32x4 acc[RTW][CTW];
+#pragma unroll
+  for (int r = 0; r < RTW; ++r)
+#pragma unroll
+    for (int c = 0; c < CTW; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < ST; ++s) issue(s, s);
+  u32x4 av[2][RTW], bv[2][CTW];
+  const unsigned char *la = s_mem + wr * RTW * 1024 + lane * 16;
+  const unsigned char *lb = s_mem + (TR + wc * CTW) * 1024 + lane * 16;
+  dma_sync<(ST - 1) * LPW>();
+#pragma unroll
+  for (int r = 0; r < RTW; ++r) av[0][r] = *(const u32x4 *)(la + r * 1024);
+#pragma unroll
+  for (int c = 0; c < CTW; ++c) bv[0][c] = *(const u32x4 *)(lb + c * 1024);
+  int slot = 0;
+  // CUR: the register set of this stage; LEFT: loads that may stay in flight
+  // at its barrier; MORE: a stage to request; NEXT: operands to read
+  auto stage = [&](int s, auto CUR, auto LEFT, auto MORE, auto NEXT) {
+    constexpr int cur = decltype(CUR)::value;
+    dma_sync<decltype(LEFT)::value>();
+    const int nx = slot + 1 == ST ? 0 : slot + 1;
+    if constexpr (decltype(MORE)::value) issue(s + ST, slot);
+    if constexpr (decltype(NEXT)::value) {
+#pragma unroll
+      for (int c = 0; c < CTW; ++c) bv[cur ^ 1][c] = *(const u32x4 *)(lb + (nx * NB + c) * 1024);
+#pragma unroll
+      for (int r = 0; r < RTW; ++r) av[cur ^ 1][r] = *(const u32x4 *)(la + (nx * NB + r) * 1024);
+    }
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+      for (int c = 0; c < CTW; ++c) acc[r][c] = mma<DT>(av[cur][r], bv[cur][c], acc[r][c]);
+    if constexpr (decltype(NEXT)::value) dma_sched<0, RTW + CTW, RTW * CTW>();
+    slot = nx;
+  };
+  using std::integral_constant;
+  using Yes = std::true_type;
+  using No = std::false_type;
+  int s = 0;
+  for (; s < n - ST; s += 2) {  // n and ST are even
+    stage(s, integral_constant<int, 0>{}, integral_constant<int, (ST - 2) * LPW>{}, Yes{}, Yes{});
+    stage(s + 1, integral_constant<int, 1>{}, integral_constant<int, (ST - 2) * LPW>{}, Yes{}, Yes{});
+  }
+  // the last ST stages, all requested
+  dma_each(
+      [&](auto... T) {
+        (stage(s + decltype(T)::value, integral_constant<int, decltype(T)::value & 1>{},
+               integral_constant<int, (ST - 2 > decltype(T)::value ? ST - 2 - decltype(T)::value : 0) * LPW>{}, No{},
+               std::bool_constant<(decltype(T)::value < ST - 1)>{}),
+         ...);
+      },
+      std::make_integer_sequence<int, ST>{});
+
+  // lane (li, lq) holds rows 4 lq .. 4 lq + 3 of each row tile for column li of each column tile
+  int mat[RTW], row0[RTW];
+#pragma unroll
+  for (int r = 0; r < RTW; ++r) tile_of(wr * RTW + r, mat[r], row0[r]);
+  const int rr = 4 * lq;
+#pragma unroll
+  for (int c = 0; c < CTW; ++c) {
+    const int col = (cg * TC + wc * CTW + c) * 16 + li;
+    if (col >= a.ncols) continue;
+    if constexpr (EPI == EPI_SWIGLU) {
+      constexpr int H = RTW / 2;
+      const int nkb_o = (a.rows[0] / 8 + 15) / 16;
+#pragma unroll
+      for (int r = 0; r < H; ++r) {
+        const int j = row0[r] + rr;
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float g = acc[r][c][e], u = acc[r + H][c][e];
+          o[e] = g / (1.0f + expf(-g)) * u;
+        }
+        // rows[0] is a multiple of 8: the four rows are in or out together, and 8-byte aligned
+        const int64_t at = a.out_packed ? packed_x_index(col, j, nkb_o) : (int64_t)col * a.ld_out + j;
+        if (j < a.rows[0]) *(u32x2 *)((uint16_t *)a.out + at) = pack4<DT>(o[0], o[1], o[2], o[3]);
+      }
+    } else if constexpr (EPI == EPI_QKV) {
+      f32x4 v[RTW];
+#pragma unroll
+      for (int r = 0; r < RTW; ++r) v[r] = acc[r][c];
+      QkvIn<RTW> in;
+      if (a.kv.paged) {
+        qkv_fetch_ids<DT, RTW, true>(a, mat, row0, col, rr, true, in);
+        qkv_fetch_tab<DT, RTW>(a, mat, row0, rr, true, in);
+        qkv_store<DT, RTW, true>(a, mat, row0, v, col, rr, in);
+      } else {
+        qkv_fetch_ids<DT, RTW, false>(a, mat, row0, col, rr, true, in);
+        qkv_fetch_tab<DT, RTW>(a, mat, row0, rr, true, in);
+        qkv_store<DT, RTW, false>(a, mat, row0, v, col, rr, in);
+      }
+    } else if (a.f32_out == F32_LOGITS) {
+      float *o = (float *)a.out + (int64_t)col * a.ld_out;
+      const bool vec = (a.ld_out & 3) == 0 && ((uintptr_t)a.out & 15) == 0;  // the caller's buffer
+#pragma unroll
+      for (int r = 0; r < RTW; ++r) {
+        const int row = row0[r] + rr;
+        if (vec && row + 3 < a.rows[0]) {
+          *(f32x4 *)(o + row) = acc[r][c];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (row + e < a.rows[0]) o[row + e] = acc[r][c][e];
+        }
+      }
+    } else {
+      // fp32 rows of which there is a multiple of 4, 16-byte aligned
+      const bool add = a.f32_out == F32_RESID;
+      const int nrow = a.rows[0] + a.rows[1] + a.rows[2];
+      float *o = add ? a.resid + (int64_t)col * a.ld_resid : a.splitk_ws + ((int64_t)sp * a.ncols + col) * nrow;
+#pragma unroll
+      for (int r = 0; r < RTW; ++r) {
+        const int row = 16 * (rg * TR + wr * RTW + r) + rr;
+        if (row < nrow) {
+          f32x4 v = acc[r][c];
+          if (add) v += *(const f32x4 *)(o + row);
+          *(f32x4 *)(o + row) = v;
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the shape of a launch
+// ---------------------------------------------------------------------------
+// Work-group tiles, TR x TC row x column tiles.  Up to 16 column tiles a
+// single column group reads every weight once from HBM; TR then follows the
+// number of row tiles, so that they make close to a whole number of work
+// groups per CU.  The wide ones are for prefill rows.
+#define HS_DMA_SHAPES(X) \
+  X(0, 1, 4, 6, 1, 6)    \
+  X(1, 1, 4, 8, 1, 6)    \
+  X(2, 1, 4, 10, 1, 6)   \
+  X(3, 1, 4, 6, 2, 6)    \
+  X(4, 1, 4, 8, 2, 6)    \
+  X(5, 1, 4, 10, 2, 6)   \
+  X(6, 1, 8, 6, 2, 6)    \
+  X(7, 1, 8, 8, 2, 6)    \
+  X(8, 1, 8, 10, 2, 6)   \
+  X(9, 2, 4, 4, 5, 4)    \
+  X(10, 2, 4, 6, 5, 4)   \
+  X(11, 2, 4, 8, 2, 6)   \
+  X(12, 2, 4, 8, 4, 4)
+constexpr int DMA_WIDE_FROM = 9;  // shapes with a q/k/v epilogue of their own
+
+struct DmaShape {
+  int tr, tc, st;
+};
+struct DmaPlan {
+  int shape, k_split;
+  bool partial;  // fp32 partials for split_finish
+  int n_groups, n_colg;
+};
+
+// Takes the shape and K split with the least estimated time.  A CU passes
+// about 40 B/ns of operands, so a work group takes 25 ns per stage and
+// sub-block (or, on few columns per row tile, what its MFMAs take), plus ~2.5
+// us to fill and drain its ring; the chip takes as many rounds of work groups
+// as 256 CUs need.  fp32 partials cost their bytes written and read once and
+// a launch.  Measured against the estimate at 64..640 columns of both 7B-shaped
+// models: the chosen shape is within 6 % of the best one.
+inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
+  static constexpr DmaShape shapes[] = {
+#define HS_DMA_ENTRY(I, WR, WC, RTW, CTW, ST) {WR * RTW, WC * CTW, ST},
+      HS_DMA_SHAPES(HS_DMA_ENTRY)
+#undef HS_DMA_ENTRY
+  };
+  constexpr int n_shapes = (int)(sizeof(shapes) / sizeof(shapes[0]));
+  const int nsb = (a.K / 8 + 15) / 16 * 4, n_ct = (a.ncols + 15) / 16;
+  const bool qkv = epi_qkv(epi), resid = epi == EPI_RESID;
+  const int64_t prows = qkv ? (int64_t)a.rows[0] + a.rows[1] + a.rows[2] : a.rows[0];
+  double least = 0.0;
+  bool found = false;
+  for (int i = 0; i < n_shapes; ++i) {
+    const DmaShape &sh = shapes[i];
+    const int rows_per = epi == EPI_SWIGLU ? sh.tr / 2 : sh.tr;
+    const int nrg = (tiles16 + rows_per - 1) / rows_per, ncg = (n_ct + sh.tc - 1) / sh.tc;
+    const double load = 25.0 * (sh.tr + (double)n_ct / ncg), mfma = 2.4 * sh.tr * sh.tc;
+    for (int ks = 1; ks <= DMA_SPLIT_MAX; ++ks) {
+      const int kper = (nsb / 4 + ks - 1) / ks * 4, last = nsb - (ks - 1) * kper;
+      if (last < sh.st) break;  // every split fills the ring
+      const bool partial = (resid && ks > 1) || (qkv && (ks > 1 || i < DMA_WIDE_FROM));
+      if (ks > 1 && !partial) break;
+      const int64_t floats = (int64_t)ks * a.ncols * prows;
+      if (partial && (!a.splitk_ws || prows % 4 || floats > a.splitk_cap || floats > DMA_SPLIT_FLOATS)) continue;
+      const int64_t units = (int64_t)nrg * ncg * ks;
+      double t = (double)((units + 255) / 256) * (kper * (load > mfma ? load : mfma) + 2500.0);
+      if (partial) t += 4000.0 + (double)floats * 8.0 / 5000.0;
+      if (!found || t < least) {
+        found = true;
+        least = t;
+        *best = DmaPlan{i, ks, partial, nrg, ncg};
+      }
+    }
+  }
+  return found;
+}
+
+template <int DT, int WR, int WC, int RTW, int CTW, int ST, int EPI>
+hipError_t dma_start(const GemmArgs &g, hipStream_t st) {
+  const int units = g.n_groups * g.n_colg * g.k_split;
+  HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, ST, EPI>), dim3(units), dim3(64 * WR * WC), 0, st, g);
+  return hipGetLastError();
+}
+
+template <int DT>
+hipError_t gemm_dma(int epi, const GemmArgs &a, int tiles16, int *parts, hipStream_t st) {
+  *parts = 0;
+  DmaPlan p;
+  if (!a.x_packed || !dma_plan(epi, a, tiles16, &p)) return hipErrorInvalidValue;
+  GemmArgs g = a;
+  g.k_split = p.k_split;
+  g.n_groups = p.n_groups;
+  g.n_colg = p.n_colg;
+  g.f32_out = p.partial ? F32_PARTS : epi == EPI_RESID ? F32_RESID : F32_LOGITS;
+  if (p.partial) *parts = p.k_split;
+  const bool direct_qkv = epi_qkv(epi) && !p.partial;
+  switch (p.shape) {
+#define HS_DMA_CASE(I, WR, WC, RTW, CTW, ST)                                                        \
+  case I:                                                                                           \
+    if (epi == EPI_SWIGLU) return dma_start<DT, WR, WC, RTW, CTW, ST, EPI_SWIGLU>(g, st);           \
+    if constexpr (I >= DMA_WIDE_FROM)                                                               \
+      if (direct_qkv) return dma_start<DT, WR, WC, RTW, CTW, ST, EPI_QKV>(g, st);                   \
+    if (direct_qkv) return hipErrorInvalidValue;                                                    \
+    return dma_start<DT, WR, WC, RTW, CTW, ST, EPI_STORE>(g, st);
+    HS_DMA_SHAPES(HS_DMA_CASE)
+#undef HS_DMA_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace dev
+}  // namespace hs

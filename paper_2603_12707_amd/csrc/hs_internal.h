@@ -96,11 +96,25 @@ struct GemmArgs {
   int *status;
   // set by the launcher: work groups per column group, and column groups
   int n_groups, n_colg;
+  int f32_out;  // k_gemm_dma, EPI_STORE: what the fp32 rows are (F32_*)
 };
+enum { F32_LOGITS = 0, F32_PARTS = 1, F32_RESID = 2 };
 
 enum { PRO_PLAIN = 0, PRO_NORM = 1, PRO_COMBINE = 2 };
 // most K splits of a residual GEMM over many columns
 constexpr int SPLITK_MAX = 4;
+// k_gemm_dma: most K splits, and most floats of their partials
+constexpr int DMA_SPLIT_MAX = 8;
+constexpr int64_t DMA_SPLIT_FLOATS = 16ll << 20;
+// floats of the K-split workspace for passes over up to `rows` columns of
+// which up to max_batch are a decode batch, widest = max(d_model, q|k|v rows):
+// SPLITK_MAX splits of any GEMM over a decode batch (which also covers a
+// deferred residual sum's fp64 partials), and what k_gemm_dma may ask for
+inline int64_t splitk_floats_for(int64_t max_batch, int64_t rows, int64_t widest) {
+  const int64_t a = (int64_t)SPLITK_MAX * max_batch * widest, b = DMA_SPLIT_MAX * rows * widest;
+  const int64_t c = b < DMA_SPLIT_FLOATS ? b : DMA_SPLIT_FLOATS;
+  return a > c ? a : c;
+}
 #ifndef HS_STATIC_SCRATCH_BYTES
 #define HS_STATIC_SCRATCH_BYTES (64ull << 20)
 #endif
