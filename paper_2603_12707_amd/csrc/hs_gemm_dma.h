@@ -61,6 +61,16 @@ __device__ __forceinline__ void dma_sched() {
   }
 }
 
+// lane row q (lanes 16 q .. 16 q + 15) holds word q of four chunks, chunk i's
+// in x_i; afterwards it holds chunk q
+__device__ __forceinline__ u32x4 transpose4(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+  const auto a = __builtin_amdgcn_permlane16_swap(x0, x1, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(x2, x3, false, false);
+  const auto c = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+  return u32x4{c[0], d[0], c[1], d[1]};
+}
+
 // f(0, 1, ...) with the numbers as types
 template <class F, int... T>
 __device__ __forceinline__ void dma_each(F f, std::integer_sequence<int, T...>) {
@@ -74,6 +84,162 @@ __device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d) {
     return u32x2{f32_to_f16(a) | (f32_to_f16(b) << 16), f32_to_f16(c) | (f32_to_f16(d) << 16)};
   else
     return u32x2{f32_to_bf16(a) | (f32_to_bf16(b) << 16), f32_to_bf16(c) | (f32_to_bf16(d) << 16)};
+}
+
+// row tile t of row group rg -> matrix and first row
+template <int EPI, int TR, int RTW>
+__device__ __forceinline__ void dma_tile(const GemmArgs &a, int rg, int t, int &m, int &r0) {
+  if constexpr (EPI == EPI_SWIGLU) {
+    constexpr int H = RTW / 2;
+    const int w = t / RTW, k = t % RTW;
+    m = k < H ? 0 : 1;
+    r0 = 16 * (rg * (TR / 2) + w * H + k % H);
+  } else {
+    int u = rg * TR + t;
+    m = 0;
+    if (a.rows[1] > 0) {  // q, k, v in turn
+      const int tq = a.rows[0] / 16, tk = a.rows[1] / 16;
+      if (u >= tq) {
+        u -= tq;
+        m = 1;
+        if (u >= tk) {
+          u -= tk;
+          m = 2;
+        }
+      }
+    }
+    r0 = 16 * u;  // past the rows in a partial last group
+  }
+}
+
+// The q/k/v epilogue of a whole work group: bias, RoPE, R(q) and the K/V
+// append.  A column's request, position, block and RoPE positions are a chain
+// of four dependent reads, so the work group makes it once, one column per
+// thread, into LDS (free after the main loop; walking it per column tile in
+// every wave cost ~60 us of each 12 x 20 tile).  The four lanes that hold one
+// column's 16 packed rows of a tile, 8 channels of each head half in 4-byte
+// words, exchange words with those of three more tiles or halves (a 4 x 4
+// transpose by row swaps), so that every lane stores one whole 16-byte chunk.
+template <int DT, int NW, int TR, int TC, int RTW, int CTW>
+__device__ __forceinline__ void dma_qkv(const GemmArgs &a, unsigned char *s_mem, int rg, int wtile0, int gcol0, int wcol0,
+                                        const int *mat, const int *row0, const f32x4 (&acc)[RTW][CTW]) {
+  static_assert(RTW % 2 == 0, "chunks in groups of four");
+  constexpr int NC = TC * 16;
+  int64_t *s_kv = (int64_t *)s_mem;            // K row of head 0 of this layer at the column's position (negative: none)
+  int *s_bh = (int *)(s_mem + NC * 8);         // elements from one KV head to the next
+  int *s_pos = s_bh + NC;                      // RoPE positions [3][NC], one per section
+  const int hd = a.head_dim, half = hd >> 1;
+  const bool per_sec = a.prefill && a.rope_m3;
+  for (int t = threadIdx.x; t < NC; t += 64 * NW) {
+    const int col = gcol0 + t;
+    const bool ok = col < a.ncols;
+    int pos, cap, bt, req;
+    int64_t base;
+    if (a.kv.paged) req = qkv_fetch_row<true>(a, ok ? col : 0, ok, pos, cap, bt, base);
+    else req = qkv_fetch_row<false>(a, ok ? col : 0, ok, pos, cap, bt, base);
+    const rsrc_t pr = qkv_pos_rsrc(a);
+    uint32_t p[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      p[s] = bld4(pr, ok ? (uint32_t)(per_sec ? s * a.rope_ld + col : req) * 4u : BUF_OOB);
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      s_pos[s * NC + t] = min(max(!a.prefill || a.rope_m3 ? (int)p[s] : pos, 0), a.rope_max - 1);
+    s_kv[t] = base < 0 ? -1 : base + ((int64_t)a.layer * 2 * a.n_kv * bt + (a.kv.paged ? pos % bt : pos)) * hd;
+    s_bh[t] = bt * hd;
+  }
+  const int lane = threadIdx.x & 63, li = lane & 15, lq = lane >> 4, rr = 4 * lq;
+  // this lane's biases (elements j0, j0 + 1 of both head halves) and table
+  // entries of every tile; where the sections split a pair of neighbours,
+  // each has its own position
+  uint32_t bias[RTW][2];
+  int j0[RTW], sec[RTW];
+  const bool odd_sec = per_sec && ((a.sec0 | a.sec1) & 1);
+#pragma unroll
+  for (int r = 0; r < RTW; ++r) {
+    const int m = mat[r], head = row0[r] / hd;
+    const bool live = row0[r] < a.rows[m];
+    j0[r] = (row0[r] - head * hd + rr) >> 1;
+    sec[r] = j0[r] < a.sec0 ? 0 : (j0[r] < a.sec1 ? 1 : 2);
+    const rsrc_t bq = make_rsrc(a.bias[m], a.bias[m] ? (uint32_t)a.rows[m] * 2u : 0u);
+    bias[r][0] = bld4(bq, live ? (uint32_t)(head * hd + j0[r]) * 2u : BUF_OOB);
+    bias[r][1] = bld4(bq, live ? (uint32_t)(head * hd + half + j0[r]) * 2u : BUF_OOB);
+  }
+  // store group s: chunks of four (tile, half) items, item lq this lane's;
+  // whole groups of four tiles take one half each, two last tiles both halves
+  constexpr int NS = RTW / 2;
+  int s_m[NS], s_head[NS], s_ch[NS];  // matrix (-1: past the rows), K/V slab, first channel
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const bool quad = s / 2 * 4 + 4 <= RTW;
+    const int r = quad ? s / 2 * 4 + lq : RTW - 2 + (lq & 1), h = quad ? s & 1 : lq >> 1;
+    int m, r0;
+    dma_tile<EPI_QKV, TR, RTW>(a, rg, wtile0 + r, m, r0);
+    const int head = r0 / hd;
+    s_m[s] = r0 < a.rows[m] ? m : -1;
+    s_head[s] = m == 2 ? a.n_kv + head : head;
+    s_ch[s] = (r0 - head * hd) / 2 + h * half;
+  }
+  __syncthreads();
+  const float *tab = a.rope_tab;
+  // cos, sin of pairs j0 and j0 + 1, one column tile ahead where the registers allow it
+  constexpr int AHEAD = RTW * CTW < 32 ? 1 : 0;
+  f32x4 cs[1 + AHEAD][RTW];
+  auto fetch = [&](int c, f32x4 *out) {
+    const int t = wcol0 + c * 16 + li;
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) {
+      if (mat[r] == 2 || row0[r] >= a.rows[mat[r]]) continue;  // wave-uniform
+      out[r] = *(const f32x4 *)(tab + 2 * ((int64_t)s_pos[sec[r] * NC + t] * half + j0[r]));
+      if (odd_sec) {
+        const int i = j0[r] + 1, s1 = i < a.sec0 ? 0 : (i < a.sec1 ? 1 : 2);
+        const float *e = tab + 2 * ((int64_t)s_pos[s1 * NC + t] * half + i);
+        out[r][2] = e[0];
+        out[r][3] = e[1];
+      }
+    }
+  };
+  if (AHEAD) fetch(0, cs[0]);
+#pragma unroll
+  for (int c = 0; c < CTW; ++c) {
+    if (!AHEAD) fetch(c, cs[0]);
+    else if (c + 1 < CTW) fetch(c + 1, cs[(c + 1) & AHEAD]);
+    const int t = wcol0 + c * 16 + li, col = gcol0 + t;
+    uint32_t w[RTW][2];
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) {
+      float o1[2], o2[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t h1 = (bias[r][0] >> (16 * e)) & 0xFFFFu, h2 = (bias[r][1] >> (16 * e)) & 0xFFFFu;
+        const float v1 = acc[r][c][2 * e] + (DT == HS_F16 ? f16_to_f32(h1) : bf16_to_f32(h1));
+        const float v2 = acc[r][c][2 * e + 1] + (DT == HS_F16 ? f16_to_f32(h2) : bf16_to_f32(h2));
+        o1[e] = v1;
+        o2[e] = v2;
+        if (mat[r] < 2) {
+          const float co = cs[c & AHEAD][r][2 * e], si = cs[c & AHEAD][r][2 * e + 1];
+          o1[e] = v1 * co - v2 * si;
+          o2[e] = v2 * co + v1 * si;
+        }
+      }
+      const u32x2 p = pack4<DT>(o1[0], o1[1], o2[0], o2[1]);
+      w[r][0] = p[0];
+      w[r][1] = p[1];
+    }
+    const int64_t kv = s_kv[t];
+    const int bh = s_bh[t];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int g = s / 2 * 4;
+      u32x4 x;
+      if (g + 4 <= RTW) x = transpose4(w[g][s & 1], w[g + 1][s & 1], w[g + 2][s & 1], w[g + 3][s & 1]);
+      else x = transpose4(w[RTW - 2][0], w[RTW - 1][0], w[RTW - 2][1], w[RTW - 1][1]);
+      if (col < a.ncols) {
+        if (s_m[s] == 0) *(u32x4 *)((uint16_t *)a.out + (int64_t)col * a.ld_out + s_head[s] * hd + s_ch[s]) = x;
+        else if (s_m[s] > 0 && kv >= 0) *(u32x4 *)((uint16_t *)a.kv.buf + kv + (int64_t)s_head[s] * bh + s_ch[s]) = x;
+      }
+    }
+  }
 }
 
 // EPI: EPI_SWIGLU; EPI_QKV (bias, RoPE, R(q), K/V append; K not split); or
@@ -109,31 +275,6 @@ void k_gemm_dma(GemmArgs a) {
   const int kper = (nsb / 4 + a.k_split - 1) / a.k_split * 4;
   const int g0 = sp * kper, n = min(nsb, g0 + kper) - g0;
 
-  // row tile t of the work group -> matrix and first row
-  auto tile_of = [&](int t, int &m, int &r0) {
-    if constexpr (EPI == EPI_SWIGLU) {
-      constexpr int H = RTW / 2;
-      const int w = t / RTW, k = t % RTW;
-      m = k < H ? 0 : 1;
-      r0 = 16 * (rg * (TR / 2) + w * H + k % H);
-    } else {
-      int u = rg * TR + t;
-      m = 0;
-      if (a.rows[1] > 0) {  // q, k, v in turn
-        const int tq = a.rows[0] / 16, tk = a.rows[1] / 16;
-        if (u >= tq) {
-          u -= tq;
-          m = 1;
-          if (u >= tk) {
-            u -= tk;
-            m = 2;
-          }
-        }
-      }
-      r0 = 16 * u;  // past the rows in a partial last group
-    }
-  };
-
   // this wave's LPW sub-blocks of every stage: row tiles first, then column
   // tiles; tiles past the data have an empty range (nothing is read, and what
   // their operands hold reaches only outputs that are not stored)
@@ -147,7 +288,7 @@ void k_gemm_dma(GemmArgs a) {
     bool in;
     if (b < TR) {
       int m, r0;
-      tile_of(b, m, r0);
+      dma_tile<EPI, TR, RTW>(a, rg, b, m, r0);
       in = r0 < a.rows[m];
       p = (uint64_t)a.w[m] + ((uint64_t)(in ? r0 >> 4 : 0) * nsb + g0) * 1024u;
     } else {
@@ -234,8 +375,12 @@ void k_gemm_dma(GemmArgs a) {
   // lane (li, lq) holds rows 4 lq .. 4 lq + 3 of each row tile for column li of each column tile
   int mat[RTW], row0[RTW];
 #pragma unroll
-  for (int r = 0; r < RTW; ++r) tile_of(wr * RTW + r, mat[r], row0[r]);
+  for (int r = 0; r < RTW; ++r) dma_tile<EPI, TR, RTW>(a, rg, wr * RTW + r, mat[r], row0[r]);
   const int rr = 4 * lq;
+  if constexpr (EPI == EPI_QKV) {
+    dma_qkv<DT, NW, TR, TC, RTW, CTW>(a, s_mem, rg, wr * RTW, cg * TC * 16, wc * CTW * 16, mat, row0, acc);
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < CTW; ++c) {
     const int col = (cg * TC + wc * CTW + c) * 16 + li;
@@ -255,20 +400,6 @@ void k_gemm_dma(GemmArgs a) {
         // rows[0] is a multiple of 8: the four rows are in or out together, and 8-byte aligned
         const int64_t at = a.out_packed ? packed_x_index(col, j, nkb_o) : (int64_t)col * a.ld_out + j;
         if (j < a.rows[0]) *(u32x2 *)((uint16_t *)a.out + at) = pack4<DT>(o[0], o[1], o[2], o[3]);
-      }
-    } else if constexpr (EPI == EPI_QKV) {
-      f32x4 v[RTW];
-#pragma unroll
-      for (int r = 0; r < RTW; ++r) v[r] = acc[r][c];
-      QkvIn<RTW> in;
-      if (a.kv.paged) {
-        qkv_fetch_ids<DT, RTW, true>(a, mat, row0, col, rr, true, in);
-        qkv_fetch_tab<DT, RTW>(a, mat, row0, rr, true, in);
-        qkv_store<DT, RTW, true>(a, mat, row0, v, col, rr, in);
-      } else {
-        qkv_fetch_ids<DT, RTW, false>(a, mat, row0, col, rr, true, in);
-        qkv_fetch_tab<DT, RTW>(a, mat, row0, rr, true, in);
-        qkv_store<DT, RTW, false>(a, mat, row0, v, col, rr, in);
       }
     } else if (a.f32_out == F32_LOGITS) {
       float *o = (float *)a.out + (int64_t)col * a.ld_out;

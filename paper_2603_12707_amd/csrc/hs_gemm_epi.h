@@ -102,9 +102,10 @@ struct QkvIn {
   float cs[R][2], sn[R][2], b1[R][2], b2[R][2];
 };
 
-template <int DT, int R, bool PAGED>
-__device__ __forceinline__ void qkv_fetch_ids(const GemmArgs &a, const int *mat, const int *row0, int col, int rr,
-                                              bool ok, QkvIn<R> &in) {
+// column col's request, position, capacity and block; returns the request
+template <bool PAGED>
+__device__ __forceinline__ int qkv_fetch_row(const GemmArgs &a, int col, bool ok, int &pos, int &cap, int &bt,
+                                             int64_t &base) {
   const bool dec = !a.prefill;
   const KvRef &kv = a.kv;
   // decode: column col is request act[col]; prefill: the packed row's request
@@ -124,23 +125,35 @@ __device__ __forceinline__ void qkv_fetch_ids(const GemmArgs &a, const int *mat,
   }
   const rsrc_t lr = make_rsrc(kv.len, dec ? nb : 0u), cr = make_rsrc(kv.cap, nb);
   const rsrc_t br = make_rsrc(kv.tab, (uint32_t)kv.ntab * 8u);
-  const rsrc_t pr = make_rsrc(a.rope_pos, dec ? nb : (a.rope_m3 ? 3u * a.rope_ld * 4u : 0u));
   const uint32_t ro = ok ? (uint32_t)req * 4u : BUF_OOB;
   const uint32_t pl = bld4(lr, dec ? ro : BUF_OOB);
-  in.cap = (int)bld4(cr, ro);
+  cap = (int)bld4(cr, ro);
   if constexpr (PAGED) {  // the block holding the position
     const rsrc_t or_ = make_rsrc(kv.toff, nb), tr = make_rsrc(kv.bt, nb);
     const int toff = (int)bld4(or_, ro);
-    in.bt = max(1, (int)bld4(tr, ro));
-    in.pos = dec ? (int)pl : ppos;
-    const u32x2 bb = bld8(br, ok && in.pos < in.cap ? (uint32_t)(toff + in.pos / in.bt) * 8u : BUF_OOB);
-    in.base = ok && in.pos < in.cap ? (int64_t)(((uint64_t)bb[1] << 32) | bb[0]) : -1;
+    bt = max(1, (int)bld4(tr, ro));
+    pos = dec ? (int)pl : ppos;
+    const u32x2 bb = bld8(br, ok && pos < cap ? (uint32_t)(toff + pos / bt) * 8u : BUF_OOB);
+    base = ok && pos < cap ? (int64_t)(((uint64_t)bb[1] << 32) | bb[0]) : -1;
   } else {  // one block per request: its start, read beside the length
     const u32x2 bb = bld8(br, ok ? (uint32_t)req * 8u : BUF_OOB);
-    in.bt = in.cap;
-    in.pos = dec ? (int)pl : ppos;
-    in.base = ok && in.pos < in.cap ? (int64_t)(((uint64_t)bb[1] << 32) | bb[0]) : -1;
+    bt = cap;
+    pos = dec ? (int)pl : ppos;
+    base = ok && pos < cap ? (int64_t)(((uint64_t)bb[1] << 32) | bb[0]) : -1;
   }
+  return req;
+}
+// the RoPE positions: of the requests (decode), of the packed rows per section (prefill M-RoPE), or not read
+__device__ __forceinline__ rsrc_t qkv_pos_rsrc(const GemmArgs &a) {
+  return make_rsrc(a.rope_pos, !a.prefill ? (uint32_t)a.kv.nreq * 4u : (a.rope_m3 ? 3u * a.rope_ld * 4u : 0u));
+}
+
+template <int DT, int R, bool PAGED>
+__device__ __forceinline__ void qkv_fetch_ids(const GemmArgs &a, const int *mat, const int *row0, int col, int rr,
+                                              bool ok, QkvIn<R> &in) {
+  const bool dec = !a.prefill;
+  const rsrc_t pr = qkv_pos_rsrc(a);
+  const int req = qkv_fetch_row<PAGED>(a, col, ok, in.pos, in.cap, in.bt, in.base);
   const int hd = a.head_dim;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
