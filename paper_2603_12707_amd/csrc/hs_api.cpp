@@ -7,6 +7,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 
 #include "hs_internal.h"
 
@@ -147,7 +148,7 @@ hipError_t rebuild_active(hs_kv *kv, hipStream_t st) {
 void free_model(hs_model *m) {
   if (!m) return;
   void *ptrs[] = {m->x,      m->q,      m->attn,    m->act,      m->hnorm,  m->splitk, m->xlast,
-                  m->pk_dev, m->logits, m->part_o, m->part_ml, m->rope_tab, m->status};
+                  m->pk_dev, m->pk_order, m->logits, m->part_o, m->part_ml, m->rope_tab, m->status};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   delete m;
@@ -184,6 +185,7 @@ struct Step {
   int S, n_split;
   hipStream_t st;
   StepWs ws;
+  int prefill_qt;  // query tiles per wave of the prefill attention
 
   // K splits the residual projection over K inputs leaves in ws.splitk for
   // the next RMSNorm to add: in decode, when the projection reads its
@@ -255,9 +257,11 @@ struct Step {
     a.n_kv = c.n_kv_heads;
     a.prefill = prefill;
     a.pk = m->pk_dev;
-    a.prefill_tiles = pk.tcu[pk.n];
-    a.prefill_pairs = 0;
-    for (int i = 0; i < pk.n; ++i) a.prefill_pairs += (pk.tcu[i + 1] - pk.tcu[i] + 1) / 2;
+    a.prefill_groups = 0;
+    for (int i = 0; i < pk.n; ++i) a.prefill_groups += pk.groups[i];
+    a.prefill_order = m->pk_order;
+    a.prefill_xh = std::gcd(c.n_kv_heads, 8);
+    a.prefill_qt = prefill_qt;
     a.S = S;
     a.n_split = n_split;
     a.part_o = ws.part_o;
@@ -472,9 +476,8 @@ int prefill_requests(hs_model *m, hs_kv *kv, int n, const int32_t *reqs, const v
       ++pk.n;
     }
     pk.cu[pk.n] = rows;
-    const int qpt = attn_prefill_rows_per_tile(c.n_heads / c.n_kv_heads);
-    for (int k = 0; k < pk.n; ++k) pk.tcu[k + 1] = pk.tcu[k] + (pk.cu[k + 1] - pk.cu[k] + qpt - 1) / qpt;
-    HIP_TRY(launch_set_packed(m->pk_dev, pk, st));
+    const int qt = attn_prefill_groups(c.n_heads / c.n_kv_heads, c.n_kv_heads, pk.n, pk.cu, pk.groups);
+    HIP_TRY(launch_set_packed(m->pk_dev, pk, m->pk_order, st));
     if (kv->pool) {  // blocks for the pass's contexts
       KvReserve r{};
       r.n = pk.n;
@@ -494,7 +497,7 @@ int prefill_requests(hs_model *m, hs_kv *kv, int n, const int32_t *reqs, const v
     }
     // every row is its own query over the rows before it in its request; no
     // splits (S covers the longest request)
-    Step pre{m, kv, rows, 1, pk, pos_thw ? pos_thw + roff : nullptr, (int)total, rows, 1, st, model_ws(m)};
+    Step pre{m, kv, rows, 1, pk, pos_thw ? pos_thw + roff : nullptr, (int)total, rows, 1, st, model_ws(m), qt};
     const int rc = pre.layers();
     if (rc) return rc;
     HIP_TRY(launch_gather_last(m->x, c.d_model, pk, m->xlast, st));
@@ -641,6 +644,7 @@ int hs_model_create(const hs_config *cfg, const hs_weights *w, int32_t max_batch
       {(void **)&m->splitk, (size_t)m->splitk_floats * 4},
       {(void **)&m->xlast, (size_t)PACK_MAX * c.d_model * 4},
       {(void **)&m->pk_dev, sizeof(PackedRows)},
+      {(void **)&m->pk_order, (size_t)prefill_groups_max(rows) * sizeof(PrefillGroup)},
       {(void **)&m->logits, w->lm_head ? (size_t)max_batch * c.vocab * 4 : 0},
       {(void **)&m->part_o, (size_t)std::max<int64_t>(entries, 1) * hd * 4},
       {(void **)&m->part_ml, (size_t)std::max<int64_t>(entries, 1) * 2 * 4},
@@ -907,10 +911,12 @@ int hs_model_reserve_rows(hs_model *m, int64_t rows) {
   if (rows <= m->rows) return HS_OK;
   const hs_config &c = m->cfg;
   const int b = dtype_bytes(c.dtype), nhd = c.n_heads * c.head_dim;
-  void *fresh[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-  const size_t bytes[5] = {(size_t)rows * c.d_model * 4, (size_t)rows * nhd * b, (size_t)act_elems(rows, nhd) * b,
-                           (size_t)act_elems(rows, c.ffn_dim) * b, (size_t)act_elems(rows, c.d_model) * b};
-  for (int i = 0; i < 5; ++i)
+  constexpr int NB = 6;
+  void *fresh[NB] = {};
+  const size_t bytes[NB] = {(size_t)rows * c.d_model * 4, (size_t)rows * nhd * b, (size_t)act_elems(rows, nhd) * b,
+                           (size_t)act_elems(rows, c.ffn_dim) * b, (size_t)act_elems(rows, c.d_model) * b,
+                            (size_t)prefill_groups_max(rows) * sizeof(PrefillGroup)};
+  for (int i = 0; i < NB; ++i)
     if (hipMalloc(&fresh[i], bytes[i]) != hipSuccess) {
       for (void *p : fresh)
         if (p) (void)hipFree(p);
@@ -923,8 +929,8 @@ int hs_model_reserve_rows(hs_model *m, int64_t rows) {
     for (void *p : fresh) (void)hipFree(p);
     return fail(HS_E_DEVICE, "hs_model_reserve_rows: device synchronisation failed");
   }
-  void **slots[5] = {(void **)&m->x, &m->q, &m->attn, &m->act, &m->hnorm};
-  for (int i = 0; i < 5; ++i) {
+  void **slots[NB] = {(void **)&m->x, &m->q, &m->attn, &m->act, &m->hnorm, (void **)&m->pk_order};
+  for (int i = 0; i < NB; ++i) {
     (void)hipFree(*slots[i]);
     *slots[i] = fresh[i];
   }

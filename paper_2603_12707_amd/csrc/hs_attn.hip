@@ -465,69 +465,69 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mma(AttnArgs a) {
 
 // Prefill attention on the matrix cores (causal: row r of the request attends
 // to rows 0..r).  The 16 MFMA columns of a query tile hold QPT = 16 / G
-// consecutive query rows x the G query heads of KV head j.  A work group
-// takes two consecutive query tiles of one request; its NW waves walk the key
-// tiles of 16 positions up to the pair's last row between them, each K/V tile
-// loaded once for both query tiles, masking the keys past each row, each wave
-// with an online softmax per query tile; the waves' states merge through LDS
-// at the end.  Operand layouts and the split of p into storage-dtype parts
-// are those of k_attn_mma, so the K/V rows a wave loads serve 2 x QPT x G
-// (query, head) pairs at once.
-// Slack (in units of the natural-log score) by which a column's scores may
-// pass the running maximum before it is raised: exp(s - m) stays below e^8.
-constexpr float RESCALE_SLACK = 8.f;
+// consecutive query rows x the G query heads of KV head j.  A work group takes
+// NW x QT consecutive query tiles of one request, QT per wave; its waves walk
+// the request's key tiles of 16 positions together, KT per step, which they
+// copy straight into LDS in MFMA operand order (K: four lanes' chunks of a
+// position apart; V: four positions of a channel chunk), one step ahead.  So a
+// K/V row read from L2 serves NW x QT x QPT query rows, and each wave keeps the
+// whole online softmax of its own columns.  Keys past a row are masked only in
+// the steps that reach the wave's rows, and steps past them are skipped.  The
+// probabilities are split into storage-dtype parts as in k_attn_mma; two key
+// tiles together make the k range of one 16x16x32 MFMA.
+//
+// What bounds it: the softmax arithmetic (about 12 vector instructions a
+// score) and the PV products (the parts double or triple them) in turn.
+//
+// Slack, in units of the base-2 exponent, by which a column's scores may pass
+// the running maximum before it is raised: exp2(s - m) stays below 2^11.5.
+constexpr float RESCALE_SLACK = 11.5f;
 
-template <int DT, int HD, int G, int NW>
+template <int DT, int HD, int G, int NW, int QT>
 __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
   static_assert(DT != HS_F32 && G <= 16 && (HD == 64 || HD == 128), "16-bit storage, at most 16 heads per group");
-  constexpr int SB = 2;
-  constexpr int CPR = HD / 8;
-  constexpr int KK = HD / 32;
-  constexpr int UB = ATTN_MMA_BATCH;
-  constexpr int QPT = 16 / G;  // query rows per tile
-  constexpr int QT = 2;        // query tiles per work group
-  static_assert(NW >= QT, "one merging wave per query tile");
+  constexpr int KT = NW;         // key tiles per step: one copied by each wave
+  constexpr int CPR = HD / 8;    // 16-byte chunks per row
+  constexpr int KK = HD / 32;    // 1 KB sub-blocks of a K tile
+  constexpr int TB = KK + 4;     // sub-blocks of a key tile (K, then V)
+  constexpr int QPT = 16 / G;    // query rows per tile
+  static_assert(KT % 2 == 0, "key tiles in pairs");
+  __shared__ __align__(1024) unsigned char s_kv[2][KT][TB * 1024];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, lg = lane >> 4;
-  // The work group's item w = (KV head j, tile pair pp).  Work groups are
-  // dealt to the 8 XCDs round robin; the order below gives each XCD one run
-  // of consecutive items, so that the query tiles of a head, which all read
-  // its K/V rows, share that XCD's L2.  Within a head the last pairs come
-  // first, so that the long causal rows start early.
-  const int np = a.prefill_pairs;
-  const int total = np * a.n_kv, nq = total >> 3, nr = total & 7;
-  const int xcd = (int)blockIdx.x & 7;
-  const int w = (xcd < nr ? xcd * (nq + 1) : nr * (nq + 1) + (xcd - nr) * nq) + ((int)blockIdx.x >> 3);
-  const int j = w / np;
-  const int pp = np - 1 - (w - j * np);
-  // packed request i holds pairs [pbase_i, pbase_i + ceil(tiles_i / 2))
-  const PackedRows *pk = a.pk;
-  int pi = 0, pbase = 0;
-  for (int k = 0; k + 1 < pk->n; ++k) {
-    const int npk = (pk->tcu[k + 1] - pk->tcu[k] + 1) >> 1;
-    if (pi == k && pp >= pbase + npk) {
-      pbase += npk;
-      pi = k + 1;
-    }
-  }
-  const int roff = pk->cu[pi], nrows = pk->cu[pi + 1] - roff;
-  const int ntiles = pk->tcu[pi + 1] - pk->tcu[pi];
-  const int req = pk->req[pi];
-  const int lt0 = 2 * (pp - pbase);  // the pair's tiles lt0, lt0 + 1 of the request (the second may not exist)
-  const int sh = li % G;             // the lane column's head
+  // The work group's item: KV head j and group `grp` of one request's query
+  // tiles.  Work groups are dealt to the 8 XCDs round robin; an XCD
+  // serves every xh-th head (xh = gcd(n_kv, 8); 8 / xh XCDs share a head's
+  // groups), so that the groups that read the same K/V rows share its L2, and
+  // takes the groups of all requests in the order of their length, longest
+  // first: in request order the last long groups ran alone at the end, and
+  // the XCDs got unequal shares.
+  const int per = a.n_kv / a.prefill_xh, share = 8 / a.prefill_xh;
+  const int xcd = (int)blockIdx.x & 7, item = (int)blockIdx.x >> 3;
+  const int j = xcd % a.prefill_xh + a.prefill_xh * (item % per);
+  const int rank = item / per * share + xcd / a.prefill_xh;
+  if (rank >= a.prefill_groups) return;
+  const PrefillGroup pg = a.prefill_order[rank];
+  const int grp = __builtin_amdgcn_readfirstlane(pg.group), req = __builtin_amdgcn_readfirstlane(pg.req);
+  const int roff = __builtin_amdgcn_readfirstlane(pg.row0), nrows = __builtin_amdgcn_readfirstlane(pg.rows);
+  const int t0 = (grp * NW + wave) * QT;                 // the wave's first query tile
+  const int sh = li % G;                                 // the lane column's head
   int sq[QT];
   bool slot[QT];
 #pragma unroll
   for (int s = 0; s < QT; ++s) {
-    sq[s] = (lt0 + s) * QPT + li / G;  // the lane column's query position in tile s
-    slot[s] = lt0 + s < ntiles && li < QPT * G && sq[s] < nrows;
+    sq[s] = (t0 + s) * QPT + li / G;  // the lane column's query position in tile s
+    slot[s] = li < QPT * G && sq[s] < nrows;
   }
-  const int qlast = min(min(lt0 + QT, ntiles) * QPT - 1, nrows - 1);  // the pair's last row
-  const int n_kt = qlast / 16 + 1;                                   // key tiles
+  // columns without a query compute a row of zeros that is not stored
+  const int wfirst = t0 * QPT;                                          // the wave's first row
+  const int wlast = wfirst < nrows ? min((t0 + QT) * QPT, nrows) - 1 : -1;  // and its last
+  const int glast = min((t0 - wave * QT + NW * QT) * QPT, nrows) - 1;   // the work group's last row
+  const int n_steps = glast / (16 * KT) + 1, last_kt = glast / 16;
   // key tiles are read block by block (a block holds a whole number of tiles)
-  const int bt = a.kv.bt[req], toff = a.kv.toff[req];
-  const int64_t kin = (int64_t)((a.layer * 2) * a.n_kv + j) * bt * HD, vin = kin + (int64_t)a.n_kv * bt * HD;
+  const int bt = __builtin_amdgcn_readfirstlane(a.kv.bt[req]), toff = __builtin_amdgcn_readfirstlane(a.kv.toff[req]);
+  const int64_t kin = (int64_t)((a.layer * 2) * a.n_kv + j) * bt * HD, vin = (int64_t)a.n_kv * bt * HD;
   const uint16_t *buf = (const uint16_t *)a.kv.buf;
 
   u32x4 qb[QT][KK];
@@ -539,173 +539,175 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
                                  (kk * 4 + lg) * 8)
                           : u32x4{0u, 0u, 0u, 0u};
 
-  float m[QT], l[QT];
+  // This wave's key tile of step s: past the group's last tile the last one
+  // again, past its last row that row again (finite values for probabilities
+  // that are zero).  A block that is not allocated reads as zeros.
+  // (same: values equal in every lane, of which the compiler cannot tell)
+  auto same = [](int64_t v) {
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+  };
+  auto tile_base = [&](int s) { return a.kv.tab[toff + min(s * KT + wave, last_kt) * 16 / bt]; };
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(&s_kv[0][wave][0]));
+  auto issue = [&](int s, int64_t base) {
+    const int64_t b0 = same(base);
+    const int p0 = min(s * KT + wave, last_kt) * 16, pb = p0 % bt;
+    const int top = min(16, glast + 1 - p0) - 1;  // the tile's last row
+    const uint32_t dst = lds0 + (s & 1) * KT * TB * 1024;
+    if (b0 < 0) {
+#pragma unroll
+      for (int x = 0; x < TB; ++x) *(u32x4 *)(&s_kv[s & 1][wave][x * 1024] + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+      return;
+    }
+    const uint64_t kp = (uint64_t)same((int64_t)(buf + b0 + kin + (int64_t)pb * HD));
+    const uint64_t vp = kp + (uint64_t)same(vin) * 2u;
+    constexpr uint32_t ROW = HD * 2, RANGE = 16 * ROW;
+    const u32x4 kr{(uint32_t)kp, (uint32_t)(kp >> 32), RANGE, (uint32_t)BUF_WORD3};
+    const u32x4 vr{(uint32_t)vp, (uint32_t)(vp >> 32), RANGE, (uint32_t)BUF_WORD3};
+    const uint32_t ko = (uint32_t)min(li, top) * ROW + lg * 16;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) dma_1k(kr, ko + kk * 64, 0, dst + kk * 1024);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      dma_1k(vr, (uint32_t)min(4 * lg + i, top) * ROW + (li % CPR) * 16, 0, dst + (KK + i) * 1024);
+  };
+
+  float m[QT], l[QT];  // running maximum (base-2 units) and this lane's share of the sum
   f32x4 o[QT][8];
 #pragma unroll
   for (int s = 0; s < QT; ++s) {
-    m[s] = -INFINITY;
+    m[s] = -1e30f;
     l[s] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[s][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-
-  // Key tiles in batches of UB per wave: the wave takes tiles kt0 + u NW +
-  // wave.  Past the pair's last key every load is empty and reads as zero.
-  constexpr int STEP = UB * NW;
-  for (int kt0 = 0; kt0 < n_kt; kt0 += STEP) {
-    u32x4 kc[UB][KK], vc[UB][4];
+  const float c2 = a.scale * 1.44269504088896341f;
+  issue(0, tile_base(0));
+  int64_t nb = tile_base(1);
+  for (int st = 0; st < n_steps; ++st) {
+    dma_sync<0>();  // this step's tiles are in LDS, and the other half is free
+    if (st + 1 < n_steps) {
+      issue(st + 1, nb);
+      nb = tile_base(st + 2);
+    }
+    const int k0 = st * KT * 16;  // the step's first key
+    if (k0 > wlast) continue;
+    const unsigned char *kv = &s_kv[st & 1][0][0] + lane * 16;
+    // independent products next to each other: an MFMA waits for the previous
+    // one on its accumulator
+    f32x4 sc[QT][KT];
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int p0 = (kt0 + u * NW + wave) * 16, blk = p0 / bt, pb = p0 - blk * bt;
-      const int64_t b0 = p0 <= qlast ? a.kv.tab[toff + blk] : -1;
-      // rows of the block up to the pair's last query position; past them, zeros
-      const uint32_t nbytes = b0 < 0 ? 0u : (uint32_t)min(bt, qlast + 1 - blk * bt) * HD * SB;
-      const rsrc_t kr = make_rsrc(buf + max(b0, (int64_t)0) + kin, nbytes);
-      const rsrc_t vr = make_rsrc(buf + max(b0, (int64_t)0) + vin, nbytes);
+    for (int u = 0; u < KT; u += 2) {
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk)
-        kc[u][kk] = bld16(kr, (uint32_t)((pb + li) * HD + (kk * 4 + lg) * 8) * SB);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        vc[u][i] = bld16(vr, li < CPR ? (uint32_t)((pb + 4 * lg + i) * HD + li * 8) * SB : BUF_OOB);
+        for (int t = 0; t < 2; ++t) {
+          const u32x4 kc = *(const u32x4 *)(kv + ((u + t) * TB + kk) * 1024);
+#pragma unroll
+          for (int s = 0; s < QT; ++s)
+            sc[s][u + t] = mma<DT>(kc, qb[s][kk], kk ? sc[s][u + t] : f32x4{0.f, 0.f, 0.f, 0.f});
+        }
     }
-    // scores of the batch's key tiles for both query tiles, their chains
-    // interleaved (past a row every score is masked and the state stays)
-    f32x4 sc[QT][UB];
-#pragma unroll
-    for (int s = 0; s < QT; ++s)
-#pragma unroll
-      for (int u = 0; u < UB; ++u) sc[s][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
+    if (k0 + KT * 16 - 1 > wfirst) {
 #pragma unroll
       for (int s = 0; s < QT; ++s)
 #pragma unroll
-        for (int u = 0; u < UB; ++u) sc[s][u] = mma<DT>(kc[u][kk], qb[s][kk], sc[s][u]);
-    u32x2 ph[QT][UB], pl[QT][UB], pt[QT][UB];
+        for (int u = 0; u < KT; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (k0 + u * 16 + 4 * lg + i > sq[s]) sc[s][u][i] = -INFINITY;
+    }
+    // o / l does not depend on the reference m as long as exp2(s - m) stays
+    // in range.  m, the same for the four lanes of a column, is raised to the
+    // column's maximum (and o, l rescaled) only when some score of the wave
+    // passes it by more than RESCALE_SLACK.
 #pragma unroll
     for (int s = 0; s < QT; ++s) {
-      float sv[UB][4];
       float tmax = -INFINITY;
 #pragma unroll
-      for (int u = 0; u < UB; ++u)
+      for (int u = 0; u < KT; ++u)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int p = (kt0 + u * NW + wave) * 16 + 4 * lg + i;
-          sv[u][i] = slot[s] && p <= sq[s] ? sc[s][u][i] * a.scale : -INFINITY;
-          tmax = fmaxf(tmax, sv[u][i]);
-        }
-      // o / l does not depend on the reference m as long as exp(s - m) stays
-      // in range.  m, the same for the four lanes of a column, is raised to
-      // the column's maximum (and o, l rescaled) only when some score of the
-      // wave passes it by more than RESCALE_SLACK.
+        for (int i = 0; i < 4; ++i) tmax = fmaxf(tmax, sc[s][u][i]);
+      tmax *= c2;
       if (__ballot(tmax > m[s] + RESCALE_SLACK)) {
         tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
         const float mn = fmaxf(m[s], tmax);
-        const float corr = m[s] == -INFINITY ? 0.f : __expf(m[s] - mn);
+        const float corr = __builtin_amdgcn_exp2f(m[s] - mn);
         l[s] *= corr;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) o[s][dt] *= corr;
         m[s] = mn;
       }
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        ph[s][u] = u32x2{0u, 0u};
-        pl[s][u] = u32x2{0u, 0u};
-        pt[s][u] = u32x2{0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float pr = sv[u][i] == -INFINITY ? 0.f : __expf(sv[u][i] - m[s]);
-          const uint32_t hb = DT == HS_F16 ? f32_to_f16(pr) : f32_to_bf16(pr);
-          const float hf = DT == HS_F16 ? f16_to_f32(hb) : bf16_to_f32(hb);
-          const uint32_t lb = DT == HS_F16 ? f32_to_f16(pr - hf) : f32_to_bf16(pr - hf);
-          const float lf = DT == HS_F16 ? f16_to_f32(lb) : bf16_to_f32(lb);
-          if constexpr (P_PARTS<DT> == 3) {  // this lane's keys only
-            const uint32_t tb = f32_to_bf16(pr - hf - lf);
-            l[s] += hf + lf + bf16_to_f32(tb);
-            pt[s][u][i >> 1] |= tb << (16 * (i & 1));
-          } else {
-            l[s] += hf + lf;
-          }
-          ph[s][u][i >> 1] |= hb << (16 * (i & 1));
-          pl[s][u][i >> 1] |= lb << (16 * (i & 1));
-        }
-      }
     }
 #pragma unroll
-    for (int u = 0; u < UB; ++u)
+    for (int u = 0; u < KT; u += 2) {
+      u32x4 ph[QT], pl[QT], pt[QT];
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        // the 16-bit element dt of keys 4 lg .. 4 lg + 3, low half first
-        const int w2 = dt >> 1;
-        const uint32_t sel = dt & 1 ? 0x07060302u : 0x05040100u;
-        u32x2 av;
-        av[0] = __builtin_amdgcn_perm(vc[u][1][w2], vc[u][0][w2], sel);
-        av[1] = __builtin_amdgcn_perm(vc[u][3][w2], vc[u][2][w2], sel);
+      for (int s = 0; s < QT; ++s)
 #pragma unroll
-        for (int s = 0; s < QT; ++s) {
-          o[s][dt] = mma16<DT>(av, ph[s][u], o[s][dt]);
-          o[s][dt] = mma16<DT>(av, pl[s][u], o[s][dt]);
-          if constexpr (P_PARTS<DT> == 3) o[s][dt] = mma16<DT>(av, pt[s][u], o[s][dt]);
+        for (int x = 0; x < 4; ++x) {  // elements 2 x, 2 x + 1 of the pair's eight keys
+          float p[2];
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[s][u + (x >> 1)][2 * (x & 1) + e], c2, -m[s]));
+            l[s] += p[e];
+          }
+          ph[s][x] = pack2<DT>(p[0], p[1]);
+          p[0] -= lo_f32<DT>(ph[s][x]);
+          p[1] -= hi_f32<DT>(ph[s][x]);
+          pl[s][x] = pack2<DT>(p[0], p[1]);
+          if constexpr (P_PARTS<DT> == 3)
+            pt[s][x] = pack2<DT>(p[0] - lo_f32<DT>(pl[s][x]), p[1] - hi_f32<DT>(pl[s][x]));
         }
+      u32x4 vc[2][4];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) vc[t][i] = *(const u32x4 *)(kv + ((u + t) * TB + KK + i) * 1024);
+#pragma unroll
+      for (int d0 = 0; d0 < 8; d0 += 2) {
+        // the 16-bit elements d0 and d0 + 1 of keys 4 lg .. 4 lg + 3 of both tiles, low half first
+        const int w2 = d0 >> 1;
+        u32x4 av[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const uint32_t sel = e ? 0x07060302u : 0x05040100u;
+            av[e][2 * t] = __builtin_amdgcn_perm(vc[t][1][w2], vc[t][0][w2], sel);
+            av[e][2 * t + 1] = __builtin_amdgcn_perm(vc[t][3][w2], vc[t][2][w2], sel);
+          }
+#pragma unroll
+        for (int part = 0; part < P_PARTS<DT>; ++part)
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int s = 0; s < QT; ++s)
+              o[s][d0 + e] = mma<DT>(av[e], part == 0 ? ph[s] : part == 1 ? pl[s] : pt[s], o[s][d0 + e]);
       }
+    }
   }
-  // l so far covers this lane's keys; the column's sum adds the four lanes
+  // lane (c, q) holds rows d = (4 q + i) * 8 + dt of its column's output: row
+  // i's elements dt = 0..7 are one 16-byte chunk, in either layout of the
+  // output.  The column's sum adds its four lanes.
 #pragma unroll
   for (int s = 0; s < QT; ++s) {
     l[s] += __shfl_xor(l[s], 16);
     l[s] += __shfl_xor(l[s], 32);
-  }
-  // merge the waves' states in wave order: M = max m_w, o = sum_w e^(m_w - M) o_w,
-  // l = sum_w e^(m_w - M) l_w; wave s merges query tile s
-  __shared__ float s_ml[NW][QT][2][64];
-  __shared__ f32x4 s_o[NW][QT][8][64];
+    if (!slot[s]) continue;
+    const float r = 1.0f / l[s];
 #pragma unroll
-  for (int s = 0; s < QT; ++s) {
-    s_ml[wave][s][0][lane] = m[s];
-    s_ml[wave][s][1][lane] = l[s];
+    for (int i = 0; i < 4; ++i) {
+      const int d = (4 * lg + i) * 8;
+      float e[8];
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) s_o[wave][s][dt][lane] = o[s][dt];
-  }
-  __syncthreads();
-  if (wave >= QT) return;
-  const int ms = wave;  // wave-uniform
-  bool my_slot = false;
-  int my_sq = 0;
-#pragma unroll
-  for (int s = 0; s < QT; ++s)
-    if (s == ms) {
-      my_slot = slot[s];
-      my_sq = sq[s];
+      for (int dt = 0; dt < 8; ++dt) {  // o / l, the product by 1 / l corrected by its remainder
+        const float v = o[s][dt][i] * r;
+        e[dt] = __builtin_fmaf(__builtin_fmaf(-v, l[s], o[s][dt][i]), r, v);
+      }
+      if (d < HD) *(u32x4 *)((uint16_t *)a.out + attn_out_at(a, roff + sq[s], (j * G + sh) * HD + d, HD)) = pack<DT>(e);
     }
-  if (!my_slot) return;
-  float M = s_ml[0][ms][0][lane];
-#pragma unroll
-  for (int w2 = 1; w2 < NW; ++w2) M = fmaxf(M, s_ml[w2][ms][0][lane]);
-  float L = 0.f;
-  f32x4 O[8];
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int w2 = 0; w2 < NW; ++w2) {
-    const float mw = s_ml[w2][ms][0][lane];
-    const float wt = mw == -INFINITY ? 0.f : __expf(mw - M);
-    L += wt * s_ml[w2][ms][1][lane];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) O[dt] += wt * s_o[w2][ms][dt][lane];
-  }
-  // lane (c, q) holds rows d = (4 q + i) * 8 + dt of its column's output
-  const int64_t orow = roff + my_sq;
-  const int ocol = (j * G + sh) * HD;
-  // row i's elements dt = 0..7 are one 16-byte chunk, in either layout of the output
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int d = (4 * lg + i) * 8;
-    float e[8];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) e[dt] = O[dt][i] / L;
-    if (d < HD) *(u32x4 *)((uint16_t *)a.out + attn_out_at(a, orow, ocol + d, HD)) = pack<DT>(e);
   }
 }
 
@@ -812,34 +814,53 @@ hipError_t combine_dt(int head_dim, int nq, const AttnArgs &a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-template <int DT, int HD>
+template <int DT, int HD, int QT>
 hipError_t prefill_hd(int group, const AttnArgs &a, hipStream_t st) {
-  constexpr int NW = 4;  // waves per query tile, taking its key tiles round robin
-  const dim3 grid(a.prefill_pairs * a.n_kv), block(64 * NW);
+  const int share = 8 / a.prefill_xh;
+  const dim3 grid((a.prefill_groups + share - 1) / share * (a.n_kv / a.prefill_xh) * 8), block(64 * PREFILL_WAVES);
   switch (group) {
-    case 1: HS_LAUNCH((k_attn_prefill<DT, HD, 1, NW>), grid, block, 0, st, a); break;
-    case 2: HS_LAUNCH((k_attn_prefill<DT, HD, 2, NW>), grid, block, 0, st, a); break;
-    case 4: HS_LAUNCH((k_attn_prefill<DT, HD, 4, NW>), grid, block, 0, st, a); break;
-    case 7: HS_LAUNCH((k_attn_prefill<DT, HD, 7, NW>), grid, block, 0, st, a); break;
-    case 8: HS_LAUNCH((k_attn_prefill<DT, HD, 8, NW>), grid, block, 0, st, a); break;
+    case 1: HS_LAUNCH((k_attn_prefill<DT, HD, 1, PREFILL_WAVES, QT>), grid, block, 0, st, a); break;
+    case 2: HS_LAUNCH((k_attn_prefill<DT, HD, 2, PREFILL_WAVES, QT>), grid, block, 0, st, a); break;
+    case 4: HS_LAUNCH((k_attn_prefill<DT, HD, 4, PREFILL_WAVES, QT>), grid, block, 0, st, a); break;
+    case 7: HS_LAUNCH((k_attn_prefill<DT, HD, 7, PREFILL_WAVES, QT>), grid, block, 0, st, a); break;
+    case 8: HS_LAUNCH((k_attn_prefill<DT, HD, 8, PREFILL_WAVES, QT>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <int DT>
+hipError_t prefill_dt(int head_dim, int group, const AttnArgs &a, hipStream_t st) {
+  const bool two = a.prefill_qt == 2;
+  if (!two && a.prefill_qt != 1) return hipErrorInvalidValue;
+  if (head_dim == 64) return two ? prefill_hd<DT, 64, 2>(group, a, st) : prefill_hd<DT, 64, 1>(group, a, st);
+  if (head_dim == 128) return two ? prefill_hd<DT, 128, 2>(group, a, st) : prefill_hd<DT, 128, 1>(group, a, st);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 bool attn_prefill_on_mma(int dtype) { return dtype != HS_F32; }
 
-int attn_prefill_rows_per_tile(int group) { return 16 / group; }
+// Query tiles per wave: two (each K/V tile read from LDS once for both) where
+// that leaves enough work groups, else one.
+constexpr int PREFILL_TWO_FROM = 512;
+int attn_prefill_groups(int group, int n_kv, int n, const int *cu, int *groups) {
+  const int qpt = 16 / group;
+  for (int qt = 2;; qt = 1) {
+    const int rows = PREFILL_WAVES * qt * qpt;
+    int64_t sum = 0;
+    for (int i = 0; i < n; ++i) sum += groups[i] = (cu[i + 1] - cu[i] + rows - 1) / rows;
+    if (qt == 1 || sum * n_kv >= PREFILL_TWO_FROM) return qt;
+  }
+}
 
 hipError_t launch_attention_prefill(int dtype, int head_dim, int group, int nrows, const AttnArgs &a,
                                     hipStream_t st) {
-  if (nrows <= 0 || a.prefill_tiles <= 0) return hipSuccess;
-  if (dtype == HS_F16) return head_dim == 64 ? prefill_hd<HS_F16, 64>(group, a, st)
-                                             : prefill_hd<HS_F16, 128>(group, a, st);
-  if (dtype == HS_BF16) return head_dim == 64 ? prefill_hd<HS_BF16, 64>(group, a, st)
-                                              : prefill_hd<HS_BF16, 128>(group, a, st);
+  if (nrows <= 0 || a.prefill_groups <= 0) return hipSuccess;
+  if (a.prefill_xh <= 0 || 8 % a.prefill_xh || a.n_kv % a.prefill_xh || !a.prefill_order) return hipErrorInvalidValue;
+  if (dtype == HS_F16) return prefill_dt<HS_F16>(head_dim, group, a, st);
+  if (dtype == HS_BF16) return prefill_dt<HS_BF16>(head_dim, group, a, st);
   return hipErrorInvalidValue;
 }
 

@@ -48,10 +48,27 @@ __device__ __forceinline__ uint32_t f32_to_f16(float f) {
 }
 __device__ __forceinline__ float bf16_to_f32(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x7FFFFFu)) return (u >> 16) | 0x40u;
-  u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest even
-  return u >> 16;
+  return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f);  // v_cvt_pk_bf16_f32, round to nearest even
+}
+// R(a) | R(b) << 16
+template <int DT>
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  if constexpr (DT == HS_F16) {
+    return f32_to_f16(a) | (f32_to_f16(b) << 16);
+  } else {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+  }
+}
+// the low and the high 16-bit element of a word
+template <int DT>
+__device__ __forceinline__ float lo_f32(uint32_t w) {
+  return DT == HS_F16 ? f16_to_f32(w & 0xFFFFu) : __uint_as_float(w << 16);
+}
+template <int DT>
+__device__ __forceinline__ float hi_f32(uint32_t w) {
+  return DT == HS_F16 ? f16_to_f32(w >> 16) : __uint_as_float(w & 0xFFFF0000u);
 }
 
 template <int DT>
@@ -75,10 +92,8 @@ __device__ __forceinline__ void st_elem2(void *p, int64_t i, float v0, float v1)
   if constexpr (DT == HS_F32) {
     ((float *)p)[i] = v0;
     ((float *)p)[i + 1] = v1;
-  } else if constexpr (DT == HS_F16) {
-    *(uint32_t *)((uint16_t *)p + i) = f32_to_f16(v0) | (f32_to_f16(v1) << 16);
   } else {
-    *(uint32_t *)((uint16_t *)p + i) = f32_to_bf16(v0) | (f32_to_bf16(v1) << 16);
+    *(uint32_t *)((uint16_t *)p + i) = pack2<DT>(v0, v1);
   }
 }
 
@@ -111,10 +126,7 @@ __device__ __forceinline__ u32x4 pack(const float *f) {
     for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(f[e]);
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if constexpr (DT == HS_F16) w[e] = f32_to_f16(f[2 * e]) | (f32_to_f16(f[2 * e + 1]) << 16);
-      else w[e] = f32_to_bf16(f[2 * e]) | (f32_to_bf16(f[2 * e + 1]) << 16);
-    }
+    for (int e = 0; e < 4; ++e) w[e] = pack2<DT>(f[2 * e], f[2 * e + 1]);
   }
   return w;
 }
@@ -197,6 +209,25 @@ __device__ __forceinline__ uint32_t bld4(rsrc_t r, uint32_t off) {
 }
 __device__ __forceinline__ u32x2 bld8(rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+
+// ---------------------------------------------------------------------------
+// loads straight to LDS
+// ---------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+__device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lds_byte *)p; }
+// Lane l's 16 bytes at voff + soff of the range go to LDS byte lds + 16 l
+// (rsrc, soff, lds wave-uniform).  No destination registers; the wait is the
+// caller's (dma_sync).
+__device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
+               "s"(rsrc), "s"(soff));
+}
+// at most N of this wave's loads still in flight, its LDS reads done, then a
+// work-group barrier
+template <int N>
+__device__ __forceinline__ void dma_sync() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
 // request (index into pk) of packed prefill row `row`

@@ -36,19 +36,6 @@ namespace dev {
 // columns runs 2.81-3.06 ms, 1250-1390 TFLOP/s; with both operands staged
 // through registers it took 4.05 ms.  A 4-wave variant with wave tiles of
 // 8 x 8 (one wave per SIMD, a quarter fewer LDS reads) took 3.82 ms.
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-
-__device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  // no destination registers: the data goes to LDS [m0 + 16 lane]
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
-               "s"(rsrc), "s"(soff));
-}
-// at most N of this wave's loads still in flight, its LDS reads done, then a
-// work-group barrier
-template <int N>
-__device__ __forceinline__ void dma_sync() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
 // NR LDS reads spread over NM MFMAs
 template <int I, int NR, int NM>
 __device__ __forceinline__ void dma_sched() {
@@ -80,10 +67,7 @@ __device__ __forceinline__ void dma_each(F f, std::integer_sequence<int, T...>) 
 // four consecutive values in the storage dtype, 8 bytes
 template <int DT>
 __device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d) {
-  if constexpr (DT == HS_F16)
-    return u32x2{f32_to_f16(a) | (f32_to_f16(b) << 16), f32_to_f16(c) | (f32_to_f16(d) << 16)};
-  else
-    return u32x2{f32_to_bf16(a) | (f32_to_bf16(b) << 16), f32_to_bf16(c) | (f32_to_bf16(d) << 16)};
+  return u32x2{pack2<DT>(a, b), pack2<DT>(c, d)};
 }
 
 // row tile t of row group rg -> matrix and first row
@@ -299,7 +283,7 @@ void k_gemm_dma(GemmArgs a) {
     rs[i] = u32x4{(uint32_t)p, (uint32_t)(p >> 32), in ? (uint32_t)n * 1024u : 0u, (uint32_t)BUF_WORD3};
     live[i] = in ? ~0u : 0u;
   }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)s_mem;
+  const uint32_t lds0 = lds_addr(s_mem);
   const uint32_t vo = (uint32_t)lane * 16u;
   // With one column group each work group starts its K range at another stage
   // (wrapping round), so that the chip's row tiles do not walk the same

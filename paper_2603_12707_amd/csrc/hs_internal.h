@@ -18,14 +18,20 @@ namespace hs {
 // The rows of one prefill pass: up to PACK_MAX requests, their rows packed
 // request by request.  Request i of the pass is KV request req[i] and owns the
 // rows cu[i] .. cu[i + 1] - 1, its positions 0 .. cu[i + 1] - cu[i] - 1.
-// tcu is set by the prefill attention launcher: request i's query tiles are
-// tcu[i] .. tcu[i + 1] - 1.
+// groups[i]: work groups per KV head of request i in the prefill attention
+// (attn_prefill_groups).
 constexpr int PACK_MAX = 32;
 struct PackedRows {
   int n;
   int cu[PACK_MAX + 1];
   int req[PACK_MAX];
-  int tcu[PACK_MAX + 1];
+  int groups[PACK_MAX];
+};
+
+// A work group of the prefill attention (for one KV head): group `group` of the
+// query tiles of request `req`, whose rows are row0 .. row0 + rows - 1.
+struct PrefillGroup {
+  int req, row0, rows, group;
 };
 
 // Where the cache rows of request (slot) r live.  Its positions are cut into
@@ -145,8 +151,10 @@ struct AttnArgs {
   int n_heads, n_kv;
   int prefill;     // 0: decode (query = column c, request act[c], length = len + 1); 1: prefill rows in *pk
   const PackedRows *pk;  // device copy; query row r of request i has length r - cu[i] + 1
-  int prefill_tiles;     // prefill: query tiles in all (pk->tcu[pk->n])
-  int prefill_pairs;     // prefill: pairs of one request's consecutive query tiles, sum of ceil(tiles / 2)
+  int prefill_groups;    // prefill: work groups per KV head (the sum of pk->groups)
+  const PrefillGroup *prefill_order;  // prefill: the groups, longest first
+  int prefill_xh;        // prefill: gcd(n_kv, 8)
+  int prefill_qt;        // prefill: query tiles per wave
   int S;           // positions per split (pooled caches: a multiple of 256)
   const int *order;  // decode: work-group row z serves column order[z] (longest first); NULL: z
   int n_split;     // splits per (query, kv head)
@@ -182,7 +190,14 @@ hipError_t launch_attention(int dtype, int head_dim, int group, int nq, const At
 hipError_t launch_combine(int dtype, int head_dim, int nq, const AttnArgs &a, hipStream_t st);
 // causal prefill attention over the packed rows of *a.pk (nrows in all), 16-bit storage; query
 // tiles of 16 / group rows
-int attn_prefill_rows_per_tile(int group);
+// causal prefill attention in work groups of PREFILL_WAVES waves: fills
+// groups[0..n) (each request's work groups per KV head) for the packed rows
+// cu[0..n]; returns the query tiles per wave
+constexpr int PREFILL_WAVES = 4;
+int attn_prefill_groups(int group, int n_kv, int n, const int *cu, int *groups);
+// most work groups per KV head of a pass of `rows` rows (a group covers at
+// least 8 rows of one request)
+inline int64_t prefill_groups_max(int64_t rows) { return rows / 8 + PACK_MAX; }
 bool attn_prefill_on_mma(int dtype);
 hipError_t launch_attention_prefill(int dtype, int head_dim, int group, int nrows, const AttnArgs &a,
                                     hipStream_t st);
@@ -235,8 +250,9 @@ hipError_t launch_set_int(int *p, int v, hipStream_t st);
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t st);
 // act = the ready requests in order (n requests)
 hipError_t launch_build_act(const int *ready, int n, int *act, hipStream_t st);
-// *dst = v, in stream order (the rows of a prefill pass, for the kernels that read them)
-hipError_t launch_set_packed(PackedRows *dst, const PackedRows &v, hipStream_t st);
+// *dst = v and order = its attention groups, longest first (AttnArgs::prefill_order), in stream order (the rows of a
+// prefill pass, for the kernels that read them)
+hipError_t launch_set_packed(PackedRows *dst, const PackedRows &v, PrefillGroup *order, hipStream_t st);
 // out[i] = x[pk.cu[i + 1] - 1] for the pk.n requests (rows of d floats)
 hipError_t launch_gather_last(const float *x, int d, const PackedRows &pk, float *out, hipStream_t st);
 
@@ -265,6 +281,7 @@ struct hs_model {
   int64_t splitk_floats = 0;
   float *xlast = nullptr;   // [PACK_MAX][d] last rows of the requests of a prefill pass
   hs::PackedRows *pk_dev = nullptr;  // the rows of the current prefill pass
+  hs::PrefillGroup *pk_order = nullptr;  // [prefill_groups_max(max_rows)] its attention groups, longest first
   float *logits = nullptr;  // [max_batch][V] (used when the caller passes no logits buffer)
   float *part_o = nullptr;
   float *part_ml = nullptr;

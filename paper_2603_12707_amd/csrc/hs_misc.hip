@@ -305,10 +305,22 @@ __global__ __launch_bounds__(256) void k_build_act(const int *ready, int n, int 
   }
 }
 
-__global__ __launch_bounds__(128) void k_set_packed(PackedRows v, PackedRows *dst) {
+// Group t of request i goes behind the groups of a higher number (a later,
+// longer stretch of its request's causal rows) and, among those of the same
+// number, behind those of the requests before it.
+__global__ __launch_bounds__(256) void k_set_packed(PackedRows v, PackedRows *dst, PrefillGroup *order) {
   constexpr int N = (int)(sizeof(PackedRows) / 4);
   const int *src = (const int *)&v;
-  for (int i = threadIdx.x; i < N; i += 128) ((int *)dst)[i] = src[i];
+  for (int i = threadIdx.x; i < N; i += 256) ((int *)dst)[i] = src[i];
+  __shared__ int s_n[PACK_MAX];
+  if (threadIdx.x < PACK_MAX) s_n[threadIdx.x] = threadIdx.x < v.n ? v.groups[threadIdx.x] : 0;
+  __syncthreads();
+  for (int i = 0; i < v.n; ++i)
+    for (int t = threadIdx.x; t < s_n[i]; t += 256) {
+      int rank = 0;
+      for (int r = 0; r < v.n; ++r) rank += max(0, s_n[r] - t - 1) + (r < i && s_n[r] > t ? 1 : 0);
+      order[rank] = PrefillGroup{v.req[i], v.cu[i], v.cu[i + 1] - v.cu[i], t};
+    }
 }
 
 __global__ __launch_bounds__(256) void k_gather_last(const float *x, int d, PackedRows pk, float *out) {
@@ -404,8 +416,8 @@ hipError_t launch_prefill_finish(int *len, int *rope_pos, int *ready, int req, i
   return hipGetLastError();
 }
 
-hipError_t launch_set_packed(PackedRows *dst, const PackedRows &v, hipStream_t st) {
-  HS_LAUNCH(k_set_packed, dim3(1), dim3(128), 0, st, v, dst);
+hipError_t launch_set_packed(PackedRows *dst, const PackedRows &v, PrefillGroup *order, hipStream_t st) {
+  HS_LAUNCH(k_set_packed, dim3(1), dim3(256), 0, st, v, dst, order);
   return hipGetLastError();
 }
 
