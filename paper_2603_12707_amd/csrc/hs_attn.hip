@@ -262,7 +262,7 @@ constexpr int P_PARTS = DT == HS_BF16 ? 3 : 2;
 // dt is element d = 8 c + dt, which a lane gathers from its four chunks.
 // The waves merge through LDS as in k_attn.
 template <int DT, int HD, int G, int NW, bool PAGED>
-__global__ __launch_bounds__(64 * NW) void k_attn_mma(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) void k_attn_mma(AttnArgs a) {
   static_assert(DT != HS_F32 && G <= 16 && (HD == 64 || HD == 128), "16-bit storage, at most 16 heads per group");
   constexpr int SB = 2;
   constexpr int CPR = HD / 8;         // 16-byte chunks per row
@@ -338,92 +338,100 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mma(AttnArgs a) {
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int it0 = 0; it0 < n_it; it0 += UB) {
-    // every K and V chunk of the batch is requested before any is used;
-    // positions past the split read zeros
-    u32x4 kc[UB][KK], vc[UB][4];
+  // A ring of UB tiles per wave: a tile's registers are requested again, for
+  // the tile UB iterations on, as soon as its products are issued, so that
+  // loads are in flight while the wave computes.  Positions past the split
+  // read zeros.
+  u32x4 kc[UB][KK], vc[UB][4];
+  bool blk_ok[UB];  // as in k_attn
+  auto request = [&](int u, int it) {
     rsrc_t kb = kr, vb = vr;
-    int rel = 0;
-    bool blk_ok = true;  // as in k_attn
-    if constexpr (PAGED) {
+    int p0 = (it * NW + wave) * 16;
+    blk_ok[u] = true;
+    if constexpr (PAGED) {  // an iteration's positions lie in one block
       const int64_t b0 = b_next;
-      blk_ok = b0 >= 0;
-      const int pb = t0 + it0 * STEP, pn = pb + UB * STEP;
+      blk_ok[u] = b0 >= 0;
+      const int pb = t0 + it * STEP, pn = pb + STEP;
       b_next = pn < t0 + n ? a.kv.tab[toff + pn / bt] : 0;
       const int64_t at = max(b0, (int64_t)0) + (int64_t)(pb % bt) * HD;
-      const uint32_t bytes = b0 < 0 ? 0u : (uint32_t)min(UB * STEP, n - it0 * STEP) * HD * SB;
+      const uint32_t bytes = b0 < 0 || it >= n_it ? 0u : (uint32_t)min(STEP, n - it * STEP) * HD * SB;
       kb = make_rsrc((const uint16_t *)a.kv.buf + at + kin, bytes);
       vb = make_rsrc((const uint16_t *)a.kv.buf + at + vin, bytes);
-      rel = it0 * STEP;
+      p0 -= it * STEP;
     }
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int p0 = ((it0 + u) * NW + wave) * 16 - rel;
+    for (int kk = 0; kk < KK; ++kk)
+      kc[u][kk] = bld16_stream(kb, (uint32_t)((p0 + li) * HD + (kk * 4 + lg) * 8) * SB);
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-        kc[u][kk] = bld16_stream(kb, (uint32_t)((p0 + li) * HD + (kk * 4 + lg) * 8) * SB);
+    for (int i = 0; i < 4; ++i)
+      vc[u][i] = bld16_stream(vb, li < CPR ? (uint32_t)((p0 + 4 * lg + i) * HD + li * 8) * SB : BUF_OOB);
+  };
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        vc[u][i] = bld16_stream(vb, li < CPR ? (uint32_t)((p0 + 4 * lg + i) * HD + li * 8) * SB : BUF_OOB);
-    }
+  for (int u = 0; u < UB; ++u) request(u, u);
+  for (int it0 = 0; it0 < n_it; it0 += UB) {
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
       const int p0 = ((it0 + u) * NW + wave) * 16;
-      f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
+      f32x4 sv = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) sc = mma<DT>(kc[u][kk], qb[kk], sc);
-      float sv[4];
+      for (int kk = 0; kk < KK; ++kk) sv = mma<DT>(kc[u][kk], qb[kk], sv);
       float tmax = -INFINITY;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        sv[i] = p0 + 4 * lg + i < n && blk_ok ? sc[i] * a.scale : -INFINITY;
+        sv[i] = p0 + 4 * lg + i < n && blk_ok[u] ? sv[i] * a.scale : -INFINITY;
         tmax = fmaxf(tmax, sv[i]);
       }
       tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
       tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
       const float mn = fmaxf(m, tmax);
       const float corr = m == -INFINITY ? 0.f : __expf(m - mn);
-      float pr[4];
+      m = mn;
+      l *= corr;  // this lane's positions only
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pr[i] = sv[i] == -INFINITY ? 0.f : __expf(sv[i] - mn);
+      for (int dt = 0; dt < 8; ++dt) o[dt] *= corr;
       // the PV operands: p = hi + lo (+ lo2 in bf16) in the storage dtype;
       // l sums the parts
-      u32x2 ph = u32x2{0u, 0u}, pl = u32x2{0u, 0u}, pt = u32x2{0u, 0u};
-      float ps = 0.f;
+      u32x2 ph, pl, pt{};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t hb = DT == HS_F16 ? f32_to_f16(pr[i]) : f32_to_bf16(pr[i]);
-        const float hf = DT == HS_F16 ? f16_to_f32(hb) : bf16_to_f32(hb);
-        const uint32_t lb = DT == HS_F16 ? f32_to_f16(pr[i] - hf) : f32_to_bf16(pr[i] - hf);
-        const float lf = DT == HS_F16 ? f16_to_f32(lb) : bf16_to_f32(lb);
+      for (int x = 0; x < 2; ++x) {
+        float p[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) p[e] = sv[2 * x + e] == -INFINITY ? 0.f : __expf(sv[2 * x + e] - m);
+        ph[x] = pack2<DT>(p[0], p[1]);
+        const float h0 = lo_f32<DT>(ph[x]), h1 = hi_f32<DT>(ph[x]);
+        pl[x] = pack2<DT>(p[0] - h0, p[1] - h1);
+        const float l0 = lo_f32<DT>(pl[x]), l1 = hi_f32<DT>(pl[x]);
         if constexpr (P_PARTS<DT> == 3) {
-          const uint32_t tb = f32_to_bf16(pr[i] - hf - lf);
-          ps += hf + lf + bf16_to_f32(tb);
-          pt[i >> 1] |= tb << (16 * (i & 1));
+          pt[x] = pack2<DT>(p[0] - h0 - l0, p[1] - h1 - l1);
+          l += (h0 + l0 + lo_f32<DT>(pt[x])) + (h1 + l1 + hi_f32<DT>(pt[x]));
         } else {
-          ps += hf + lf;
+          l += (h0 + l0) + (h1 + l1);
         }
-        ph[i >> 1] |= hb << (16 * (i & 1));
-        pl[i >> 1] |= lb << (16 * (i & 1));
       }
-      ps += __shfl_xor(ps, 16);
-      ps += __shfl_xor(ps, 32);
-      l = l * corr + ps;
-      m = mn;
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        o[dt] *= corr;
-        // V^T rows: element dt of chunk lane % 16 of the 4 positions
-        const int w = dt >> 1, sh = 16 * (dt & 1);
-        u32x2 av;
-        av[0] = ((vc[u][0][w] >> sh) & 0xFFFFu) | (((vc[u][1][w] >> sh) & 0xFFFFu) << 16);
-        av[1] = ((vc[u][2][w] >> sh) & 0xFFFFu) | (((vc[u][3][w] >> sh) & 0xFFFFu) << 16);
-        o[dt] = mma16<DT>(av, ph, o[dt]);
-        o[dt] = mma16<DT>(av, pl, o[dt]);
-        if constexpr (P_PARTS<DT> == 3) o[dt] = mma16<DT>(av, pt, o[dt]);
+      for (int d0 = 0; d0 < 8; d0 += 2) {
+        // V^T rows: the 16-bit elements d0 and d0 + 1 of chunk lane % 16 of the 4 positions
+        const int w = d0 >> 1;
+        u32x2 av[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const uint32_t sel = e ? 0x07060302u : 0x05040100u;
+          av[e][0] = __builtin_amdgcn_perm(vc[u][1][w], vc[u][0][w], sel);
+          av[e][1] = __builtin_amdgcn_perm(vc[u][3][w], vc[u][2][w], sel);
+        }
+#pragma unroll
+        for (int part = 0; part < P_PARTS<DT>; ++part)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) o[d0 + e] = mma16<DT>(av[e], part == 0 ? ph : part == 1 ? pl : pt, o[d0 + e]);
       }
+      // kept apart: the compiler gathers both tiles' operands first and sinks the requests to the loop's end
+      __builtin_amdgcn_sched_barrier(0);
+      request(u, it0 + u + UB);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
 
   __shared__ float s_m[NW][16], s_l[NW][16];
   __shared__ float s_o[NW][16][HD + 1];
@@ -728,21 +736,19 @@ __global__ __launch_bounds__(HD) void k_combine(AttnArgs a) {
 #pragma unroll
     for (int sp = 0; sp < NSF; ++sp) {
       const u32x2 ml = bld8(mr, (uint32_t)sp * 8u);
-      m[sp] = __uint_as_float(ml[0]);
-      l[sp] = __uint_as_float(ml[1]);
+      m[sp] = sp < ns ? __uint_as_float(ml[0]) : -INFINITY;  // past the splits: weight zero, no branch
+      l[sp] = __uint_as_float(ml[1]);                        // (one would let its loads be put behind it)
       o[sp] = __uint_as_float(bld4(orr, (uint32_t)(sp * HD + e) * 4u));
     }
     float M = -INFINITY;
 #pragma unroll
-    for (int sp = 0; sp < NSF; ++sp)
-      if (sp < ns) M = fmaxf(M, m[sp]);
+    for (int sp = 0; sp < NSF; ++sp) M = fmaxf(M, m[sp]);
 #pragma unroll
-    for (int sp = 0; sp < NSF; ++sp)
-      if (sp < ns) {
-        const float w = expf(m[sp] - M);
-        den += w * l[sp];
-        num += w * o[sp];
-      }
+    for (int sp = 0; sp < NSF; ++sp) {
+      const float w = expf(m[sp] - M);
+      den += w * l[sp];
+      num += w * o[sp];
+    }
   } else {
     __shared__ float s_m[ATTN_MAX_SPLITS], s_w[ATTN_MAX_SPLITS];
     for (int sp = e; sp < ns; sp += HD) s_m[sp] = a.part_ml[(base + sp) * 2];
