@@ -136,13 +136,15 @@ hipError_t rebuild_order(hs_kv *kv, hipStream_t st) {
 }
 
 // the ready requests, in order, as the decode columns (pooled caches)
-hipError_t rebuild_active(hs_kv *kv, hipStream_t st) {
+void list_active(hs_kv *kv) {
   kv->act_host.clear();
   for (int r = 0; r < kv->batch; ++r)
     if (kv->ready[r]) kv->act_host.push_back(r);
   kv->n_active = (int)kv->act_host.size();
-  const hipError_t e = launch_build_act(kv->d_ready, kv->batch, kv->d_act, st);
-  return e != hipSuccess ? e : rebuild_order(kv, st);
+}
+hipError_t rebuild_active(hs_kv *kv, hipStream_t st) {
+  list_active(kv);
+  return launch_build_active(kv->d_ready, kv->batch, kv->d_len, kv->n_active, kv->d_act, kv->d_order, st);
 }
 
 void free_model(hs_model *m) {
@@ -477,24 +479,13 @@ int prefill_requests(hs_model *m, hs_kv *kv, int n, const int32_t *reqs, const v
     }
     pk.cu[pk.n] = rows;
     const int qt = attn_prefill_groups(c.n_heads / c.n_kv_heads, c.n_kv_heads, pk.n, pk.cu, pk.groups);
-    HIP_TRY(launch_set_packed(m->pk_dev, pk, m->pk_order, st));
-    if (kv->pool) {  // blocks for the pass's contexts
-      KvReserve r{};
-      r.n = pk.n;
-      for (int k = 0; k < pk.n; ++k) {
-        r.req[k] = pk.req[k];
-        r.target[k] = pk.cu[k + 1] - pk.cu[k];
-      }
-      HIP_TRY(launch_kv_reserve(kv_pool(kv), r, 0, st));
-    }
-    for (int k = 0; k < pk.n; ++k) {
-      const int nv = kv->n_v[pk.req[k]], nt = s_text[i0 + k];
-      HIP_TRY(launch_prefill_rows(c.dtype, (const char *)emb + voff * c.d_model * b, nv, m->w.embed, c.vocab,
-                                  c.d_model, text_ids ? text_ids + toff : nullptr, nt, m->x + (int64_t)pk.cu[k] * c.d_model,
-                                  m->status, st));
-      voff += nv;
-      toff += nt;
-    }
+    for (int k = 0; k < pk.n; ++k) pk.vis[k + 1] = pk.vis[k] + kv->n_v[pk.req[k]];
+    const KvPool pool = kv_pool(kv);  // takes the blocks for the pass's contexts
+    HIP_TRY(launch_prefill_begin(pk, m->pk_dev, m->pk_order, kv->pool ? &pool : nullptr, st));
+    HIP_TRY(launch_prefill_rows(c.dtype, (const char *)emb + voff * c.d_model * b, m->w.embed, c.vocab, c.d_model,
+                                text_ids + toff, m->pk_dev, rows, m->x, m->status, st));
+    voff += pk.vis[pk.n];
+    toff += rows - pk.vis[pk.n];
     // every row is its own query over the rows before it in its request; no
     // splits (S covers the longest request)
     Step pre{m, kv, rows, 1, pk, pos_thw ? pos_thw + roff : nullptr, (int)total, rows, 1, st, model_ws(m), qt};
@@ -506,9 +497,8 @@ int prefill_requests(hs_model *m, hs_kv *kv, int n, const int32_t *reqs, const v
     last.ncols = pk.n;
     HIP_TRY(last.head(m->xlast, lg, 0));
     HIP_TRY(launch_argmax(lg, c.vocab, c.vocab, pk.n, first_tokens + i0, nullptr, nullptr, nullptr, 0, st));
-    for (int k = 0; k < pk.n; ++k)
-      HIP_TRY(launch_prefill_finish(kv->d_len, kv->d_rope, kv->d_ready, pk.req[k], pk.cu[k + 1] - pk.cu[k],
-                                    pos_thw ? pos_thw + roff + pk.cu[k] : nullptr, (int)total, st));
+    HIP_TRY(launch_prefill_finish(kv->d_len, kv->d_rope, kv->d_ready, m->pk_dev, pk.n, pos_thw ? pos_thw + roff : nullptr,
+                                  (int)total, st));
     for (int k = 0; k < pk.n; ++k) {
       const int req = pk.req[k], s_ctx = pk.cu[k + 1] - pk.cu[k];
       kv->len[req] = s_ctx;
@@ -866,14 +856,14 @@ int hs_kv_release(hs_kv *kv, int32_t slot, hs_stream_t stream) {
   if (slot < 0 || slot >= kv->batch) return fail(HS_E_INVALID, "hs_kv_release: slot %d out of range", slot);
   if (kv->cap[slot] == 0) return fail(HS_E_STATE, "hs_kv_release: slot %d is empty", slot);
   hipStream_t st = (hipStream_t)stream;
-  HIP_TRY(launch_kv_release(kv_pool(kv), slot, st));
-  HIP_TRY(launch_set_int(kv->d_cap + slot, 0, st));
   const bool was_ready = kv->ready[slot];
+  // the pool's handle has a list of decode columns without this one
+  HIP_TRY(launch_kv_release(kv_pool(kv), slot, kv->batch, was_ready ? kv->n_active - 1 : -1, kv->d_act, kv->d_order, st));
   kv->free_blocks += kv->nblk[slot];
   kv->nblk[slot] = 0;
   kv->n_v[slot] = kv->cap[slot] = kv->len[slot] = kv->rope[slot] = 0;
   kv->ready[slot] = 0;
-  if (was_ready) HIP_TRY(rebuild_active(kv, st));
+  if (was_ready) list_active(kv);
   return HS_OK;
 }
 

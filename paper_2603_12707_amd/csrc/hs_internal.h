@@ -21,9 +21,12 @@ namespace hs {
 // groups[i]: work groups per KV head of request i in the prefill attention
 // (attn_prefill_groups).
 constexpr int PACK_MAX = 32;
+// Request i's vision rows are vis[i] .. vis[i + 1] - 1 of the pass's embedding
+// rows.
 struct PackedRows {
   int n;
   int cu[PACK_MAX + 1];
+  int vis[PACK_MAX + 1];
   int req[PACK_MAX];
   int groups[PACK_MAX];
 };
@@ -204,24 +207,25 @@ hipError_t launch_attention_prefill(int dtype, int head_dim, int group, int nrow
 // x[c] = E[tokens[act[c]]] (act NULL: tokens[c])
 hipError_t launch_embed(int dtype, const void *embed, int vocab, int d, const int *tokens, const int *act, int n,
                         float *x, int *status, hipStream_t st);
-hipError_t launch_prefill_rows(int dtype, const void *emb, int n_v, const void *embed, int vocab, int d,
-                               const int *ids, int s_text, float *x, int *status, hipStream_t st);
+// x = the rows of a prefill pass: vision rows from emb, text rows embed[ids]
+hipError_t launch_prefill_rows(int dtype, const void *emb, const void *embed, int vocab, int d, const int *ids,
+                               const PackedRows *pk, int rows, float *x, int *status, hipStream_t st);
 // row c's argmax to tokens_out[act[c]] (act NULL: [c]); with advance, that
 // request's length and RoPE position += 1
 hipError_t launch_argmax(const float *logits, int vocab, int ld, int n, int *tokens_out, const int *act, int *len,
                          int *rope_pos, int advance, hipStream_t st);
 hipError_t launch_advance(int *len, int *rope_pos, const int *act, int n, hipStream_t st);
-// len[req] = s_ctx, the next RoPE position, ready[req] = 1; pos_thw: [3][ld]
-// section-major, this request's s_ctx columns
-hipError_t launch_prefill_finish(int *len, int *rope_pos, int *ready, int req, int s_ctx, const int *pos_thw, int ld,
-                                 hipStream_t st);
+// for the n requests of a pass: len = its rows, the next RoPE position, ready = 1; pos_thw: [3][ld] section-major,
+// the pass's columns
+hipError_t launch_prefill_finish(int *len, int *rope_pos, int *ready, const PackedRows *pk, int n, const int *pos_thw,
+                                 int ld, hipStream_t st);
 
 // Block pool of a KV handle: a stack of free block ids on the device, and per
 // request the count of blocks it holds (its table entries toff[r] ..).
 struct KvPool {
   int64_t *tab;
-  const int *toff, *cap;
-  int *len, *rope, *ready, *nblk, *stack, *top, *status;
+  const int *toff;
+  int *cap, *len, *rope, *ready, *nblk, *stack, *top, *status;
   const int *act;
   int bt;              // positions per block
   int64_t block_elems; // elements per block
@@ -237,8 +241,9 @@ struct KvReserve {
 // len + 1 (capped at capacity).  A shortfall sets status bit 4 and leaves
 // those requests' entries unallocated.
 hipError_t launch_kv_reserve(const KvPool &p, const KvReserve &r, int decode_n, hipStream_t st);
-// returns request req's blocks to the stack and empties it (length 0, not ready)
-hipError_t launch_kv_release(const KvPool &p, int req, hipStream_t st);
+// returns request req's blocks to the stack and empties it (length and capacity 0, not ready); n_active >= 0: then
+// lists the n_active decode columns that stay, of n requests, as launch_build_active
+hipError_t launch_kv_release(const KvPool &p, int req, int n, int n_active, int *act, int *order, hipStream_t st);
 // order = the n decode columns by decreasing length (ties: lower column
 // first); column c is request act[c] (act NULL: c)
 hipError_t launch_build_order(const int *len, const int *act, int n, int *order, hipStream_t st);
@@ -248,11 +253,13 @@ hipError_t launch_stream_read(const void *buf, uint64_t bytes, uint32_t *sink, i
 hipError_t launch_set_int(int *p, int v, hipStream_t st);
 // zeroes bytes (a multiple of 16, 16-byte aligned) at p, in stream order
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t st);
-// act = the ready requests in order (n requests)
-hipError_t launch_build_act(const int *ready, int n, int *act, hipStream_t st);
-// *dst = v and order = its attention groups, longest first (AttnArgs::prefill_order), in stream order (the rows of a
-// prefill pass, for the kernels that read them)
-hipError_t launch_set_packed(PackedRows *dst, const PackedRows &v, PrefillGroup *order, hipStream_t st);
+// act = the n_active ready requests of n, in order; order: as launch_build_order
+hipError_t launch_build_active(const int *ready, int n, const int *len, int n_active, int *act, int *order,
+                               hipStream_t st);
+// starts a prefill pass: *dst = v, order = its attention groups, longest first (AttnArgs::prefill_order), and, with a
+// pool, the blocks that cover its contexts (a shortfall as launch_kv_reserve)
+hipError_t launch_prefill_begin(const PackedRows &v, PackedRows *dst, PrefillGroup *order, const KvPool *pool,
+                                hipStream_t st);
 // out[i] = x[pk.cu[i + 1] - 1] for the pk.n requests (rows of d floats)
 hipError_t launch_gather_last(const float *x, int d, const PackedRows &pk, float *out, hipStream_t st);
 

@@ -50,17 +50,22 @@ __global__ __launch_bounds__(256) void k_embed(const void *E, int V, int d, cons
   copy_row<DT>((const char *)E + (int64_t)t * d * B, x + (int64_t)b * d, d);
 }
 
+// Row r of a prefill pass: its request's vision rows from emb, then its text
+// rows from the embedding table (emb and ids of all the pass's requests).
 template <int DT>
-__global__ __launch_bounds__(256) void k_prefill_rows(const void *emb, int n_v, const void *E, int V, int d,
-                                                      const int *ids, float *x, int *status) {
-  const int r = blockIdx.x;
+__global__ __launch_bounds__(256) void k_prefill_rows(const void *emb, const void *E, int V, int d, const int *ids,
+                                                      const PackedRows *pk, float *x, int *status) {
+  const int r = blockIdx.x, lane = threadIdx.x & 63;
+  const int first = lane < pk->n ? pk->cu[lane] : INT32_MAX;
+  const int i = (int)__popcll(__ballot(r >= first)) - 1;
+  const int at = r - pk->cu[i], v0 = pk->vis[i], n_v = pk->vis[i + 1] - v0;
   const void *src;
   int64_t row;
-  if (r < n_v) {
+  if (at < n_v) {
     src = emb;
-    row = r;
+    row = v0 + at;
   } else {
-    int t = ids[r - n_v];
+    int t = ids[r - v0 - n_v];
     if (t < 0 || t >= V) {
       if (threadIdx.x == 0) atomicOr(status, 1);
       t = 0;
@@ -135,12 +140,15 @@ __global__ void k_advance(int *len, int *rope, const int *act, int n) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_prefill_finish(int *len, int *rope, int *ready, int req, int s_ctx,
+// Work group i: request i of the pass holds its context from now on.  pos_thw:
+// the pass's columns.
+__global__ __launch_bounds__(256) void k_prefill_finish(int *len, int *rope, int *ready, const PackedRows *pk,
                                                         const int *pos_thw, int ld) {
+  const int r0 = pk->cu[blockIdx.x], s_ctx = pk->cu[blockIdx.x + 1] - r0, req = pk->req[blockIdx.x];
   int mx = s_ctx - 1;
   if (pos_thw) {
     mx = 0x80000000;
-    for (int i = threadIdx.x; i < 3 * s_ctx; i += 256) mx = max(mx, pos_thw[(i / s_ctx) * ld + i % s_ctx]);
+    for (int i = threadIdx.x; i < 3 * s_ctx; i += 256) mx = max(mx, pos_thw[(i / s_ctx) * ld + r0 + i % s_ctx]);
     for (int off = 32; off >= 1; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
     __shared__ int s_mx[4];
     if ((threadIdx.x & 63) == 0) s_mx[threadIdx.x >> 6] = mx;
@@ -177,18 +185,18 @@ __device__ int block_scan(int v, int *s_tmp, int *total) {
 // Block allocation: each listed request takes the blocks between what it holds
 // and what covers its target length, from the top of the free stack, in list
 // order (a prefix sum hands out disjoint stack ranges, so no atomics).
-__global__ __launch_bounds__(256) void k_kv_reserve(KvPool p, KvReserve r, int decode_n) {
+template <class Entry>
+__device__ void reserve_blocks(const KvPool &p, int n, Entry entry) {
   __shared__ int s_tmp[4];
   __shared__ int s_top, s_used;
   if (threadIdx.x == 0) s_top = *p.top;
   __syncthreads();
-  const int n = decode_n > 0 ? decode_n : r.n;
   for (int c0 = 0; c0 < n; c0 += 256) {
     const int c = c0 + threadIdx.x;
     int req = -1, need = 0, held = 0;
     if (c < n) {
-      req = decode_n > 0 ? p.act[c] : r.req[c];
-      const int target = decode_n > 0 ? min(p.len[req] + 1, p.cap[req]) : r.target[c];
+      int target;
+      entry(c, req, target);
       held = p.nblk[req];
       need = max(0, (target + p.bt - 1) / p.bt - held);
     }
@@ -217,7 +225,67 @@ __global__ __launch_bounds__(256) void k_kv_reserve(KvPool p, KvReserve r, int d
   if (threadIdx.x == 0) *p.top = s_top;
 }
 
-__global__ __launch_bounds__(256) void k_kv_release(KvPool p, int req) {
+__global__ __launch_bounds__(256) void k_kv_reserve(KvPool p, KvReserve r, int decode_n) {
+  if (decode_n > 0)
+    reserve_blocks(p, decode_n, [&](int c, int &req, int &target) {
+      req = p.act[c];
+      target = min(p.len[req] + 1, p.cap[req]);
+    });
+  else
+    reserve_blocks(p, r.n, [&](int c, int &req, int &target) {
+      req = r.req[c];
+      target = r.target[c];
+    });
+}
+
+// Columns by decreasing length: a column's rank is the number of columns ahead
+// of it, longer, or as long with a lower index.  n^2 comparisons in one work
+// group (n <= a few thousand, once per change of the batch), the lengths read
+// through LDS.
+__device__ void build_order(const int *len, const int *act, int n, int *order) {
+  __shared__ int s_len[256];
+  for (int c0 = 0; c0 < n; c0 += 256) {
+    const int c = c0 + threadIdx.x, lc = c < n ? len[act ? act[c] : c] : 0;
+    int rank = 0;
+    for (int o0 = 0; o0 < n; o0 += 256) {
+      const int x = o0 + threadIdx.x, m = min(256, n - o0);
+      __syncthreads();
+      if (x < n) s_len[threadIdx.x] = len[act ? act[x] : x];
+      __syncthreads();
+      for (int o = 0; o < m; ++o) rank += s_len[o] > lc || (s_len[o] == lc && o0 + o < c);
+    }
+    if (c < n) order[rank] = c;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_build_order(const int *len, const int *act, int n, int *order) {
+  build_order(len, act, n, order);
+}
+
+// act = the n_active ready requests of n, in order, and their dispatch order
+__device__ void build_active(const int *ready, int n, const int *len, int n_active, int *act, int *order) {
+  __shared__ int s_tmp[4];
+  int base = 0;
+  for (int c0 = 0; c0 < n; c0 += 256) {
+    const int c = c0 + threadIdx.x;
+    const int f = c < n && ready[c] ? 1 : 0;
+    int total;
+    const int off = block_scan(f, s_tmp, &total);
+    if (f) act[base + off] = c;
+    base += total;
+  }
+  __syncthreads();
+  build_order(len, act, n_active, order);
+}
+
+__global__ __launch_bounds__(256) void k_build_active(const int *ready, int n, const int *len, int n_active, int *act,
+                                                      int *order) {
+  build_active(ready, n, len, n_active, act, order);
+}
+
+// n_active >= 0: the request was a decode column, and the n_active that stay
+// are listed anew
+__global__ __launch_bounds__(256) void k_kv_release(KvPool p, int req, int n, int n_active, int *act, int *order) {
   const int held = p.nblk[req], top = *p.top;
   for (int k = threadIdx.x; k < held; k += 256) {
     const int64_t start = p.tab[p.toff[req] + k];
@@ -231,22 +299,11 @@ __global__ __launch_bounds__(256) void k_kv_release(KvPool p, int req) {
     p.len[req] = 0;
     p.rope[req] = 0;
     p.ready[req] = 0;
+    p.cap[req] = 0;
   }
-}
-
-// Column c's rank is the number of columns ahead of it: longer, or as long
-// with a lower index.  n^2 comparisons in one work group (n <= a few
-// thousand, once per change of the batch).
-__global__ __launch_bounds__(256) void k_build_order(const int *len, const int *act, int n, int *order) {
-  for (int c = threadIdx.x; c < n; c += 256) {
-    const int lc = len[act ? act[c] : c];
-    int rank = 0;
-    for (int o = 0; o < n; ++o) {
-      const int lo = len[act ? act[o] : o];
-      rank += lo > lc || (lo == lc && o < c);
-    }
-    order[rank] = c;
-  }
+  if (n_active < 0) return;
+  __syncthreads();
+  build_active(p.ready, n, p.len, n_active, act, order);
 }
 
 // A plain streaming read (the HBM read rate the kernels are measured
@@ -292,23 +349,14 @@ __global__ __launch_bounds__(256) void k_zero(u32x4 *p, int64_t n16) {
     p[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
-__global__ __launch_bounds__(256) void k_build_act(const int *ready, int n, int *act) {
-  __shared__ int s_tmp[4];
-  int base = 0;
-  for (int c0 = 0; c0 < n; c0 += 256) {
-    const int c = c0 + threadIdx.x;
-    const int f = c < n && ready[c] ? 1 : 0;
-    int total;
-    const int off = block_scan(f, s_tmp, &total);
-    if (f) act[base + off] = c;
-    base += total;
-  }
-}
-
+// The tables of a prefill pass, and (pooled caches) the blocks for its
+// contexts.
+//
 // Group t of request i goes behind the groups of a higher number (a later,
 // longer stretch of its request's causal rows) and, among those of the same
 // number, behind those of the requests before it.
-__global__ __launch_bounds__(256) void k_set_packed(PackedRows v, PackedRows *dst, PrefillGroup *order) {
+__global__ __launch_bounds__(256) void k_prefill_begin(PackedRows v, PackedRows *dst, PrefillGroup *order,
+                                                       KvPool p, int pool) {
   constexpr int N = (int)(sizeof(PackedRows) / 4);
   const int *src = (const int *)&v;
   for (int i = threadIdx.x; i < N; i += 256) ((int *)dst)[i] = src[i];
@@ -321,6 +369,11 @@ __global__ __launch_bounds__(256) void k_set_packed(PackedRows v, PackedRows *ds
       for (int r = 0; r < v.n; ++r) rank += max(0, s_n[r] - t - 1) + (r < i && s_n[r] > t ? 1 : 0);
       order[rank] = PrefillGroup{v.req[i], v.cu[i], v.cu[i + 1] - v.cu[i], t};
     }
+  if (pool)
+    reserve_blocks(p, v.n, [&](int c, int &req, int &target) {
+      req = v.req[c];
+      target = v.cu[c + 1] - v.cu[c];
+    });
 }
 
 __global__ __launch_bounds__(256) void k_gather_last(const float *x, int d, PackedRows pk, float *out) {
@@ -343,14 +396,13 @@ hipError_t launch_embed(int dtype, const void *embed, int vocab, int d, const in
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_rows(int dtype, const void *emb, int n_v, const void *embed, int vocab, int d,
-                               const int *ids, int s_text, float *x, int *status, hipStream_t st) {
-  const int rows = n_v + s_text;
+hipError_t launch_prefill_rows(int dtype, const void *emb, const void *embed, int vocab, int d, const int *ids,
+                               const PackedRows *pk, int rows, float *x, int *status, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   switch (dtype) {
-    case HS_F32: HS_LAUNCH(k_prefill_rows<HS_F32>, dim3(rows), dim3(256), 0, st, emb, n_v, embed, vocab, d, ids, x, status); break;
-    case HS_F16: HS_LAUNCH(k_prefill_rows<HS_F16>, dim3(rows), dim3(256), 0, st, emb, n_v, embed, vocab, d, ids, x, status); break;
-    case HS_BF16: HS_LAUNCH(k_prefill_rows<HS_BF16>, dim3(rows), dim3(256), 0, st, emb, n_v, embed, vocab, d, ids, x, status); break;
+    case HS_F32: HS_LAUNCH(k_prefill_rows<HS_F32>, dim3(rows), dim3(256), 0, st, emb, embed, vocab, d, ids, pk, x, status); break;
+    case HS_F16: HS_LAUNCH(k_prefill_rows<HS_F16>, dim3(rows), dim3(256), 0, st, emb, embed, vocab, d, ids, pk, x, status); break;
+    case HS_BF16: HS_LAUNCH(k_prefill_rows<HS_BF16>, dim3(rows), dim3(256), 0, st, emb, embed, vocab, d, ids, pk, x, status); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -375,8 +427,8 @@ hipError_t launch_kv_reserve(const KvPool &p, const KvReserve &r, int decode_n, 
   return hipGetLastError();
 }
 
-hipError_t launch_kv_release(const KvPool &p, int req, hipStream_t st) {
-  HS_LAUNCH(k_kv_release, dim3(1), dim3(256), 0, st, p, req);
+hipError_t launch_kv_release(const KvPool &p, int req, int n, int n_active, int *act, int *order, hipStream_t st) {
+  HS_LAUNCH(k_kv_release, dim3(1), dim3(256), 0, st, p, req, n, n_active, act, order);
   return hipGetLastError();
 }
 
@@ -404,20 +456,23 @@ hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_build_act(const int *ready, int n, int *act, hipStream_t st) {
+hipError_t launch_build_active(const int *ready, int n, const int *len, int n_active, int *act, int *order,
+                               hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  HS_LAUNCH(k_build_act, dim3(1), dim3(256), 0, st, ready, n, act);
+  HS_LAUNCH(k_build_active, dim3(1), dim3(256), 0, st, ready, n, len, n_active, act, order);
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_finish(int *len, int *rope_pos, int *ready, int req, int s_ctx, const int *pos_thw, int ld,
-                                 hipStream_t st) {
-  HS_LAUNCH(k_prefill_finish, dim3(1), dim3(256), 0, st, len, rope_pos, ready, req, s_ctx, pos_thw, ld);
+hipError_t launch_prefill_finish(int *len, int *rope_pos, int *ready, const PackedRows *pk, int n, const int *pos_thw,
+                                 int ld, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  HS_LAUNCH(k_prefill_finish, dim3(n), dim3(256), 0, st, len, rope_pos, ready, pk, pos_thw, ld);
   return hipGetLastError();
 }
 
-hipError_t launch_set_packed(PackedRows *dst, const PackedRows &v, PrefillGroup *order, hipStream_t st) {
-  HS_LAUNCH(k_set_packed, dim3(1), dim3(256), 0, st, v, dst, order);
+hipError_t launch_prefill_begin(const PackedRows &v, PackedRows *dst, PrefillGroup *order, const KvPool *pool,
+                                hipStream_t st) {
+  HS_LAUNCH(k_prefill_begin, dim3(1), dim3(256), 0, st, v, dst, order, pool ? *pool : KvPool{}, pool ? 1 : 0);
   return hipGetLastError();
 }
 
