@@ -223,6 +223,11 @@ __device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t voff, uint32_t soff,
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
                "s"(rsrc), "s"(soff));
 }
+// non-temporal: data read once per launch (weights under a single column group)
+__device__ __forceinline__ void dma_1k_stream(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff),
+               "s"(rsrc), "s"(soff));
+}
 // at most N of this wave's loads still in flight, its LDS reads done, then a
 // work-group barrier
 template <int N>

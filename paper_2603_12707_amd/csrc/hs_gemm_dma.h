@@ -20,18 +20,27 @@ namespace dev {
 //
 // A work group of WR x WC waves owns TR = WR RTW row tiles and TC = WC CTW
 // column tiles; wave (wr, wc) computes RTW x CTW of them over the work group's
-// K range.  K advances in stages of one sub-block through a ring of ST stages
-// in LDS.  At stage s a wave waits for its own loads of stage s + 1 (the
-// counter then still covers ST - 2 stages), meets the others at one barrier,
-// requests stage s + ST into the slot that stage s leaves (its operands are in
-// registers since the stage before), reads the operands of stage s + 1, and
-// issues the MFMAs of stage s, the reads spread between them.
+// K range.  K advances in stages of KS sub-blocks through a ring of ST stages
+// in LDS.  A wave reads the operands of the next sub-block while it issues the
+// MFMAs of the present one, the reads spread between them.  At a stage's last
+// sub-block it waits for its own loads of the next stage (the counter then
+// still covers ST - 2 stages), meets the others at one barrier, and requests
+// the stage ST on into the slot that this one leaves (its operands are in
+// registers by then).
 //
-// What bounds it.  Per CU about 38-40 B/ns of operand loads pass (weights from
-// HBM and activations from L2 together, whatever the ring depth from 4 to 18
-// stages), so a tile's time is its bytes, 1 KB x (TR + TC) per stage, and the
-// launcher takes the shape with the fewest bytes per CU that still fills the
-// chip.  At the largest tile (16 x 16) that is as long as the power limit
+// The shapes of decode batches take two sub-blocks per stage: half the
+// barriers, and 2 KB of a row tile requested at a time; where a single column
+// group reads the weights, they are loaded with the non-temporal hint.  Decode
+// layer: 120 requests 297 -> 277 us, 75 326 -> 314, 256 623 -> 610; gate/up
+// over 75 columns (22016 x 4096) 52.9 -> 42.9 us, over 120 (37888 x 3584)
+// 60.7 -> 54.7, over 256 85.6 -> 80.2.  The loads alone, in this order without
+// the arithmetic, take 35-37 and 48 us there.
+//
+// What bounds it.  In decode about 36-40 B/ns of operands pass per CU: weights
+// from HBM (6.1 TB/s, 24 B/ns per CU, is all that loads alone reach) and
+// activations from L2 together (those alone reach 128 B/ns), so a tile's time
+// is about its bytes, 1 KB x (TR + TC) per sub-block, and the launcher takes
+// the shape with the fewest bytes per CU that still fills the chip.  At the largest tile (16 x 16) that is as long as the power limit
 // leaves the matrix cores (1.9 GHz, MFMA 65 % busy): 37888 x 3584 over 14400
 // columns runs 2.81-3.06 ms, 1250-1390 TFLOP/s; with both operands staged
 // through registers it took 4.05 ms.  A 4-wave variant with wave tiles of
@@ -229,14 +238,22 @@ __device__ __forceinline__ void dma_qkv(const GemmArgs &a, unsigned char *s_mem,
 // EPI: EPI_SWIGLU; EPI_QKV (bias, RoPE, R(q), K/V append; K not split); or
 // EPI_STORE, fp32 rows by a.f32_out: logits, K-split partials (residual rows,
 // or q|k|v rows in turn), or the residual add
-template <int DT, int WR, int WC, int RTW, int CTW, int ST, int EPI>
+template <int DT, int WR, int WC, int RTW, int CTW, int KS, int ST, int EPI, bool NT>
 __global__ __launch_bounds__(64 * WR * WC) __attribute__((amdgpu_waves_per_eu(WR * WC / 4, 2)))
 void k_gemm_dma(GemmArgs a) {
   constexpr int NW = WR * WC, TR = WR * RTW, TC = WC * CTW;
-  constexpr int NB = TR + TC;               // sub-blocks per stage
-  constexpr int LPW = (NB + NW - 1) / NW;   // of them moved per wave
-  constexpr bool PAD = LPW * NW > NB;       // some waves move an empty one (their counters agree)
-  static_assert(ST % 2 == 0 && (ST - 1) * LPW <= 63, "ring depth");
+  constexpr int NB = (TR + TC) * KS;        // sub-blocks per stage
+  // Of them moved per wave: row tiles' first, column tiles' after.  With
+  // several sub-blocks per stage each kind is dealt out by itself (LA and LB
+  // loads per wave), so that a load's kind, and with it the cache hint, is
+  // known at compile time; some waves may move empty ones (their counters
+  // agree).
+  constexpr bool APART = KS > 1;
+  constexpr int LA = APART ? (TR * KS + NW - 1) / NW : 0, LB = APART ? (TC * KS + NW - 1) / NW : (NB + NW - 1) / NW;
+  constexpr int LPW = LA + LB;
+  constexpr bool PAD = APART ? LA * NW > TR * KS || LB * NW > TC * KS : LB * NW > NB;
+  static_assert((KS > 1 ? KS % 2 == 0 : ST % 2 == 0) && (ST - 1) * LPW <= 63, "ring depth");
+  static_assert(!NT || APART, "the hint needs the kinds apart");
   static_assert(EPI != EPI_SWIGLU || RTW % 2 == 0, "gate/up pairs per wave");
   __shared__ __align__(1024) unsigned char s_mem[(ST * NB + (PAD ? 1 : 0)) * 1024];
   const int lane = threadIdx.x & 63;
@@ -255,33 +272,38 @@ void k_gemm_dma(GemmArgs a) {
   const int sp = unit / per, u0 = unit - sp * per;
   const int sr = u0 / (SH * ncg), sh = min(SH, nrg - sr * SH), u1 = u0 - sr * SH * ncg;
   const int rg = sr * SH + u1 % sh, cg = u1 / sh;
-  // this split's stages [g0, g0 + n): whole k-blocks of 4, at least ST (the launcher sees to it)
+  // this split's sub-blocks [g0, g0 + ns), whole k-blocks of 4, in n stages, at least ST (the launcher sees to it)
   const int kper = (nsb / 4 + a.k_split - 1) / a.k_split * 4;
-  const int g0 = sp * kper, n = min(nsb, g0 + kper) - g0;
+  const int g0 = sp * kper, ns = min(nsb, g0 + kper) - g0, n = ns / KS;
 
-  // this wave's LPW sub-blocks of every stage: row tiles first, then column
-  // tiles; tiles past the data have an empty range (nothing is read, and what
-  // their operands hold reaches only outputs that are not stored)
+  // this wave's LPW sub-blocks of every stage; tiles past the data have an
+  // empty range (nothing is read, and what their operands hold reaches only
+  // outputs that are not stored)
   u32x4 rs[LPW];
-  uint32_t live[LPW];
+  uint32_t live[LPW], ldst[LPW];
   const int n_ct = (a.ncols + 15) >> 4;
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    const int b = wave * LPW + i;
+    const int b = !APART ? wave * LPW + i : i < LA ? wave * LA + i : TR * KS + wave * LB + i - LA;
+    const bool row = APART ? i < LA : b < TR;
+    const bool pad = b >= (row ? TR * KS : NB);
+    const int t = pad ? 0 : b / KS, k = b % KS;
     uint64_t p;
     bool in;
-    if (b < TR) {
+    if (row) {
       int m, r0;
-      dma_tile<EPI, TR, RTW>(a, rg, b, m, r0);
+      dma_tile<EPI, TR, RTW>(a, rg, t, m, r0);
       in = r0 < a.rows[m];
-      p = (uint64_t)a.w[m] + ((uint64_t)(in ? r0 >> 4 : 0) * nsb + g0) * 1024u;
+      p = (uint64_t)a.w[m] + ((uint64_t)(in ? r0 >> 4 : 0) * nsb + g0 + k) * 1024u;
     } else {
-      const int ct = cg * TC + b - TR;
-      in = b < NB && ct < n_ct;
-      p = (uint64_t)a.x + ((uint64_t)(in ? ct : 0) * nsb + g0) * 1024u;
+      const int ct = cg * TC + t - TR;
+      in = !pad && ct < n_ct;
+      p = (uint64_t)a.x + ((uint64_t)(in ? ct : 0) * nsb + g0 + k) * 1024u;
     }
-    rs[i] = u32x4{(uint32_t)p, (uint32_t)(p >> 32), in ? (uint32_t)n * 1024u : 0u, (uint32_t)BUF_WORD3};
+    in = in && !pad;
+    rs[i] = u32x4{(uint32_t)p, (uint32_t)(p >> 32), in ? (uint32_t)(ns - k) * 1024u : 0u, (uint32_t)BUF_WORD3};
     live[i] = in ? ~0u : 0u;
+    ldst[i] = PAD && pad ? ~0u : (uint32_t)b * 1024u;
   }
   const uint32_t lds0 = lds_addr(s_mem);
   const uint32_t vo = (uint32_t)lane * 16u;
@@ -296,9 +318,9 @@ void k_gemm_dma(GemmArgs a) {
     g -= g >= n ? n : 0;
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-      const int b = wave * LPW + i;
-      const uint32_t dst = PAD && b >= NB ? (uint32_t)(ST * NB) : (uint32_t)(slot * NB + b);
-      dma_1k(rs[i], vo, (uint32_t)g * 1024u & live[i], lds0 + dst * 1024u);
+      const uint32_t dst = PAD && ldst[i] == ~0u ? (uint32_t)(ST * NB) * 1024u : (uint32_t)(slot * NB) * 1024u + ldst[i];
+      if (NT && i < LA) dma_1k_stream(rs[i], vo, (uint32_t)g * (KS * 1024u) & live[i], lds0 + dst);
+      else dma_1k(rs[i], vo, (uint32_t)g * (KS * 1024u) & live[i], lds0 + dst);
     }
   };
 
@@ -310,46 +332,60 @@ void k_gemm_dma(GemmArgs a) {
 #pragma unroll
   for (int s = 0; s < ST; ++s) issue(s, s);
   u32x4 av[2][RTW], bv[2][CTW];
-  const unsigned char *la = s_mem + wr * RTW * 1024 + lane * 16;
-  const unsigned char *lb = s_mem + (TR + wc * CTW) * 1024 + lane * 16;
+  const unsigned char *la = s_mem + wr * RTW * KS * 1024 + lane * 16;
+  const unsigned char *lb = s_mem + (TR + wc * CTW) * KS * 1024 + lane * 16;
   dma_sync<(ST - 1) * LPW>();
 #pragma unroll
-  for (int r = 0; r < RTW; ++r) av[0][r] = *(const u32x4 *)(la + r * 1024);
+  for (int r = 0; r < RTW; ++r) av[0][r] = *(const u32x4 *)(la + r * KS * 1024);
 #pragma unroll
-  for (int c = 0; c < CTW; ++c) bv[0][c] = *(const u32x4 *)(lb + c * 1024);
+  for (int c = 0; c < CTW; ++c) bv[0][c] = *(const u32x4 *)(lb + c * KS * 1024);
   int slot = 0;
-  // CUR: the register set of this stage; LEFT: loads that may stay in flight
-  // at its barrier; MORE: a stage to request; NEXT: operands to read
-  auto stage = [&](int s, auto CUR, auto LEFT, auto MORE, auto NEXT) {
+  // the MFMAs of the operands in set `cur`, and meanwhile the reads of the
+  // sub-block at `at` (bytes into a tile's place in the ring) into the other
+  auto step = [&](auto CUR, auto NEXT, int at) {
     constexpr int cur = decltype(CUR)::value;
-    dma_sync<decltype(LEFT)::value>();
-    const int nx = slot + 1 == ST ? 0 : slot + 1;
-    if constexpr (decltype(MORE)::value) issue(s + ST, slot);
     if constexpr (decltype(NEXT)::value) {
 #pragma unroll
-      for (int c = 0; c < CTW; ++c) bv[cur ^ 1][c] = *(const u32x4 *)(lb + (nx * NB + c) * 1024);
+      for (int c = 0; c < CTW; ++c) bv[cur ^ 1][c] = *(const u32x4 *)(lb + at + c * KS * 1024);
 #pragma unroll
-      for (int r = 0; r < RTW; ++r) av[cur ^ 1][r] = *(const u32x4 *)(la + (nx * NB + r) * 1024);
+      for (int r = 0; r < RTW; ++r) av[cur ^ 1][r] = *(const u32x4 *)(la + at + r * KS * 1024);
     }
 #pragma unroll
     for (int r = 0; r < RTW; ++r)
 #pragma unroll
       for (int c = 0; c < CTW; ++c) acc[r][c] = mma<DT>(av[cur][r], bv[cur][c], acc[r][c]);
     if constexpr (decltype(NEXT)::value) dma_sched<0, RTW + CTW, RTW * CTW>();
-    slot = nx;
   };
   using std::integral_constant;
   using Yes = std::true_type;
   using No = std::false_type;
+  // CUR: the register set of the stage's first sub-block; LEFT: loads that may
+  // stay in flight at its barrier; MORE: a stage to request; NEXT: a stage
+  // whose first operands to read.  The barrier stands before the last
+  // sub-block's MFMAs: by then every wave has the stage's operands in
+  // registers.
+  auto stage = [&](int s, auto CUR, auto LEFT, auto MORE, auto NEXT) {
+    constexpr int cur = decltype(CUR)::value;
+    dma_each(
+        [&](auto... T) { (step(integral_constant<int, (cur + decltype(T)::value) & 1>{}, Yes{}, (slot * NB + decltype(T)::value + 1) * 1024), ...); },
+        std::make_integer_sequence<int, KS - 1>{});
+    dma_sync<decltype(LEFT)::value>();
+    const int nx = slot + 1 == ST ? 0 : slot + 1;
+    if constexpr (decltype(MORE)::value) issue(s + ST, slot);
+    step(integral_constant<int, (cur + KS - 1) & 1>{}, NEXT, nx * NB * 1024);
+    slot = nx;
+  };
+  constexpr int ODD = KS % 2;  // with one sub-block per stage the register sets change from stage to stage
   int s = 0;
-  for (; s < n - ST; s += 2) {  // n and ST are even
+  for (; s < n - ST; s += 1 + ODD) {  // ODD: n and ST are even
     stage(s, integral_constant<int, 0>{}, integral_constant<int, (ST - 2) * LPW>{}, Yes{}, Yes{});
-    stage(s + 1, integral_constant<int, 1>{}, integral_constant<int, (ST - 2) * LPW>{}, Yes{}, Yes{});
+    if constexpr (ODD)
+      stage(s + 1, integral_constant<int, 1>{}, integral_constant<int, (ST - 2) * LPW>{}, Yes{}, Yes{});
   }
   // the last ST stages, all requested
   dma_each(
       [&](auto... T) {
-        (stage(s + decltype(T)::value, integral_constant<int, decltype(T)::value & 1>{},
+        (stage(s + decltype(T)::value, integral_constant<int, decltype(T)::value & ODD>{},
                integral_constant<int, (ST - 2 > decltype(T)::value ? ST - 2 - decltype(T)::value : 0) * LPW>{}, No{},
                std::bool_constant<(decltype(T)::value < ST - 1)>{}),
          ...);
@@ -424,24 +460,24 @@ void k_gemm_dma(GemmArgs a) {
 // single column group reads every weight once from HBM; TR then follows the
 // number of row tiles, so that they make close to a whole number of work
 // groups per CU.  The wide ones are for prefill rows.
-#define HS_DMA_SHAPES(X) \
-  X(0, 1, 4, 6, 1, 6)    \
-  X(1, 1, 4, 8, 1, 6)    \
-  X(2, 1, 4, 10, 1, 6)   \
-  X(3, 1, 4, 6, 2, 6)    \
-  X(4, 1, 4, 8, 2, 6)    \
-  X(5, 1, 4, 10, 2, 6)   \
-  X(6, 1, 8, 6, 2, 6)    \
-  X(7, 1, 8, 8, 2, 6)    \
-  X(8, 1, 8, 10, 2, 6)   \
-  X(9, 2, 4, 4, 5, 4)    \
-  X(10, 2, 4, 6, 5, 4)   \
-  X(11, 2, 4, 8, 2, 6)   \
-  X(12, 2, 4, 8, 4, 4)
+#define HS_DMA_SHAPES(X)   \
+  X(0, 1, 4, 6, 1, 2, 4)   \
+  X(1, 1, 4, 8, 1, 2, 4)   \
+  X(2, 1, 4, 10, 1, 2, 4)  \
+  X(3, 1, 4, 6, 2, 2, 4)   \
+  X(4, 1, 4, 8, 2, 2, 4)   \
+  X(5, 1, 4, 10, 2, 2, 4)  \
+  X(6, 1, 8, 6, 2, 2, 3)   \
+  X(7, 1, 8, 8, 2, 2, 3)   \
+  X(8, 1, 8, 10, 2, 2, 3)  \
+  X(9, 2, 4, 4, 5, 1, 4)   \
+  X(10, 2, 4, 6, 5, 1, 4)  \
+  X(11, 2, 4, 8, 2, 1, 6)  \
+  X(12, 2, 4, 8, 4, 1, 4)
 constexpr int DMA_WIDE_FROM = 9;  // shapes with a q/k/v epilogue of their own
 
 struct DmaShape {
-  int tr, tc, st;
+  int tr, tc, fill;  // fill: sub-blocks of K that fill the ring
 };
 struct DmaPlan {
   int shape, k_split;
@@ -458,7 +494,7 @@ struct DmaPlan {
 // models: the chosen shape is within 6 % of the best one.
 inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
   static constexpr DmaShape shapes[] = {
-#define HS_DMA_ENTRY(I, WR, WC, RTW, CTW, ST) {WR * RTW, WC * CTW, ST},
+#define HS_DMA_ENTRY(I, WR, WC, RTW, CTW, KS, ST) {WR * RTW, WC * CTW, KS * ST},
       HS_DMA_SHAPES(HS_DMA_ENTRY)
 #undef HS_DMA_ENTRY
   };
@@ -475,7 +511,7 @@ inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
     const double load = 25.0 * (sh.tr + (double)n_ct / ncg), mfma = 2.4 * sh.tr * sh.tc;
     for (int ks = 1; ks <= DMA_SPLIT_MAX; ++ks) {
       const int kper = (nsb / 4 + ks - 1) / ks * 4, last = nsb - (ks - 1) * kper;
-      if (last < sh.st) break;  // every split fills the ring
+      if (last < sh.fill) break;  // every split fills the ring
       const bool partial = (resid && ks > 1) || (qkv && (ks > 1 || i < DMA_WIDE_FROM));
       if (ks > 1 && !partial) break;
       const int64_t floats = (int64_t)ks * a.ncols * prows;
@@ -493,10 +529,16 @@ inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
   return found;
 }
 
-template <int DT, int WR, int WC, int RTW, int CTW, int ST, int EPI>
+template <int DT, int WR, int WC, int RTW, int CTW, int KS, int ST, int EPI>
 hipError_t dma_start(const GemmArgs &g, hipStream_t st) {
-  const int units = g.n_groups * g.n_colg * g.k_split;
-  HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, ST, EPI>), dim3(units), dim3(64 * WR * WC), 0, st, g);
+  const dim3 units(g.n_groups * g.n_colg * g.k_split), block(64 * WR * WC);
+  // weights that one column group reads alone are not kept in the caches
+  if constexpr (KS > 1)
+    if (g.n_colg == 1) {
+      HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, KS, ST, EPI, true>), units, block, 0, st, g);
+      return hipGetLastError();
+    }
+  HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, KS, ST, EPI, false>), units, block, 0, st, g);
   return hipGetLastError();
 }
 
@@ -513,13 +555,13 @@ hipError_t gemm_dma(int epi, const GemmArgs &a, int tiles16, int *parts, hipStre
   if (p.partial) *parts = p.k_split;
   const bool direct_qkv = epi_qkv(epi) && !p.partial;
   switch (p.shape) {
-#define HS_DMA_CASE(I, WR, WC, RTW, CTW, ST)                                                        \
+#define HS_DMA_CASE(I, WR, WC, RTW, CTW, KS, ST)                                                    \
   case I:                                                                                           \
-    if (epi == EPI_SWIGLU) return dma_start<DT, WR, WC, RTW, CTW, ST, EPI_SWIGLU>(g, st);           \
+    if (epi == EPI_SWIGLU) return dma_start<DT, WR, WC, RTW, CTW, KS, ST, EPI_SWIGLU>(g, st);           \
     if constexpr (I >= DMA_WIDE_FROM)                                                               \
-      if (direct_qkv) return dma_start<DT, WR, WC, RTW, CTW, ST, EPI_QKV>(g, st);                   \
+      if (direct_qkv) return dma_start<DT, WR, WC, RTW, CTW, KS, ST, EPI_QKV>(g, st);                   \
     if (direct_qkv) return hipErrorInvalidValue;                                                    \
-    return dma_start<DT, WR, WC, RTW, CTW, ST, EPI_STORE>(g, st);
+    return dma_start<DT, WR, WC, RTW, CTW, KS, ST, EPI_STORE>(g, st);
     HS_DMA_SHAPES(HS_DMA_CASE)
 #undef HS_DMA_CASE
   }
