@@ -1,0 +1,131 @@
+"""Small cases at the edges of the wide GEMM's work-group tiles and of the prefill attention's work groups, against the
+oracle: the q/k/v epilogue that walks a column's metadata once per work group (RoPE sections that split a pair of
+neighbours, biases, ragged columns, contiguous and pooled caches), decode batches around its column tiles, and key
+steps, query tiles and requests that end inside a step."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from helpers import KV_ROW0_TOL, LOGIT_TOL, Pair, rel_err, small_cfg, token_ok
+
+pytestmark = pytest.mark.gpu
+TDT = {"f16": torch.float16, "bf16": torch.bfloat16}
+
+
+def _prefill(cfg, shapes, pool):
+    """Prefills the requests (n_v, s_text) in one pass; returns the cache, the oracle's sequences and their tokens
+    after checking every request's logits, first token and layer-0 K/V rows."""
+    import paper_2603_12707_amd as hs
+    n = len(shapes)
+    caps = [a + b + 4 for a, b in shapes]
+    pair = Pair(cfg, max_batch=n, max_ctx=max(caps))
+    pair.gpu.reserve_rows(sum(a + b for a, b in shapes))
+    if pool:
+        kv = hs.KVPool(pair.gpu, n, 256, sum(-(-c // 256) for c in caps))
+        for r, (n_v, _) in enumerate(shapes):
+            kv.admit(r, n_v, caps[r])
+    else:
+        kv = hs.KVCache(pair.gpu, [a for a, _ in shapes], caps)
+    ins = [pair.request_inputs(r, a, b) for r, (a, b) in enumerate(shapes)]
+    embs, ids = [e for e, _, _ in ins if e.shape[0]], [i for _, i, _ in ins if i.shape[0]]
+    pos = torch.cat([p for _, _, p in ins], dim=1).contiguous().cuda() if cfg["rope_kind"] == 1 else None
+    logits = torch.empty(n, cfg["vocab"], dtype=torch.float32, device="cuda")
+    toks = kv.prefill_batch(list(range(n)), torch.cat(embs).cuda() if embs else None,
+                            torch.cat(ids).cuda() if ids else None, [b for _, b in shapes], pos, last_logits=logits)
+    torch.cuda.synchronize()
+    toks, got = toks.cpu().tolist(), logits.cpu().numpy()
+    seqs, nxt = [], []
+    for r, (n_v, s_text) in enumerate(shapes):
+        s = pair.ora.new_seq(caps[r])
+        emb, i, p = ins[r]
+        ref, tok = s.prefill(emb if n_v else None, i, p)
+        assert rel_err(got[r], ref) <= LOGIT_TOL, (r, rel_err(got[r], ref))
+        assert token_ok(toks[r], got[r], ref)[0], (r, toks[r], tok)
+        for at in {0, (n_v + s_text) // 2, n_v + s_text - 1}:
+            for h in {0, cfg["n_kv_heads"] - 1}:
+                for sel in range(2):
+                    row = torch.empty(1, cfg["head_dim"], dtype=TDT[cfg["dtype"]], device="cuda")
+                    kv.read(r, 0, sel, h, at, 1, row)
+                    err = rel_err(row.float().cpu().numpy(), s.read_kv(0, sel, h, at, 1))
+                    assert err <= KV_ROW0_TOL, (r, at, h, sel, err)
+        seqs.append(s)
+        nxt.append(tok)
+    return pair, kv, seqs, nxt
+
+
+# (heads, KV heads, head_dim, M-RoPE sections or None, bias, dtype, pooled)
+PREFILLS = {
+    "mha_f16": (8, 8, 128, None, 0, "f16", False),
+    "gqa7_odd_sections_bf16_pool": (14, 2, 128, (15, 26, 23), 1, "bf16", True),
+    "gqa4_hd64_f16_pool": (8, 2, 64, (7, 12, 13), 0, "f16", True),
+    "gqa8_bf16": (8, 1, 128, None, 1, "bf16", False),
+    "gqa2_hd64_bf16": (6, 3, 64, (8, 12, 12), 1, "bf16", False),
+}
+
+
+@pytest.mark.parametrize("name", list(PREFILLS))
+@pytest.mark.parametrize("shapes", [[(33, 1)], [(1, 63), (0, 65), (40, 88), (0, 1)], [(250, 63), (17, 3), (129, 128)]],
+                         ids=["one_34", "mixed_258", "ragged_590"])
+def test_prefill_edges(name, shapes):
+    nh, nkv, hd, sec, bias, dtype, pool = PREFILLS[name]
+    cfg = small_cfg(n_layers=1, d_model=512, n_heads=nh, n_kv_heads=nkv, head_dim=hd, ffn_dim=520, vocab=307,
+                    dtype=dtype, qkv_bias=bias, rope_kind=1 if sec else 0, mrope_section=sec or (0, 0, 0))
+    pair, kv, _, _ = _prefill(cfg, shapes, pool)
+    assert pair.gpu.status() == 0
+    kv.close()
+    pair.gpu.close()
+
+
+@pytest.mark.parametrize("batch", [33, 65, 129])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_decode_batches(batch, dtype):
+    """One decode step over batches just past a column tile: K ranges of whole and of a partial k-block (d 640, F 1000),
+    with their splits, after a packed prefill of as many requests."""
+    cfg = small_cfg(n_layers=1, d_model=640, n_heads=8, n_kv_heads=2, head_dim=64, ffn_dim=1000, vocab=301, dtype=dtype,
+                    qkv_bias=1)
+    shapes = [(r % 5, 1 + r % 3) for r in range(batch)]
+    pair, kv, seqs, nxt = _prefill(cfg, shapes, False)
+    tin = torch.tensor(nxt, dtype=torch.int32, device="cuda")
+    tout = torch.empty_like(tin)
+    logits = torch.empty(batch, cfg["vocab"], dtype=torch.float32, device="cuda")
+    kv.decode(tin, tout, logits)
+    torch.cuda.synchronize()
+    got, toks = logits.cpu().numpy(), tout.cpu().tolist()
+    for r in range(batch):
+        ref, _, tok = seqs[r].decode(nxt[r])
+        assert rel_err(got[r], ref) <= LOGIT_TOL, (r, rel_err(got[r], ref))
+        assert token_ok(toks[r], got[r], ref)[0], (r, toks[r], tok)
+    assert pair.gpu.status() == 0
+    kv.close()
+    pair.gpu.close()
+
+
+def test_release_keeps_the_other_requests():
+    """Admission, a packed prefill, releases in any order and a second pass in the freed slots: the decode columns that
+    stay are those of the requests that stay."""
+    cfg = small_cfg(n_layers=1, d_model=512, n_heads=8, n_kv_heads=8, head_dim=64, ffn_dim=520, vocab=307, dtype="f16")
+    shapes = [(5, 4), (0, 30), (300, 7), (2, 2)]
+    pair, kv, seqs, nxt = _prefill(cfg, shapes, True)
+    for gone in (2, 0):
+        kv.release(gone)
+    live = [1, 3]
+    assert [n > 0 for n in kv.lengths()] == [r in live for r in range(4)]
+    tin = torch.tensor([nxt[r] if r in live else 0 for r in range(4)], dtype=torch.int32, device="cuda")
+    tout = torch.full_like(tin, -7)
+    logits = torch.empty(2, cfg["vocab"], dtype=torch.float32, device="cuda")
+    kv.decode(tin, tout, logits)
+    torch.cuda.synchronize()
+    got, toks = logits.cpu().numpy(), tout.cpu().tolist()
+    for k, r in enumerate(live):
+        ref, _, tok = seqs[r].decode(nxt[r])
+        assert rel_err(got[k], ref) <= LOGIT_TOL
+        assert token_ok(toks[r], got[k], ref)[0], (r, toks[r], tok)
+    assert toks[0] == toks[2] == -7
+    kv.release(3)
+    kv.release(1)
+    free, total = kv.blocks()
+    assert free == total and kv.lengths() == [0, 0, 0, 0]
+    kv.close()
+    pair.gpu.close()
