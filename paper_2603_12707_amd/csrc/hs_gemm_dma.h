@@ -79,6 +79,16 @@ __device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d) {
   return u32x2{pack2<DT>(a, b), pack2<DT>(c, d)};
 }
 
+// Work unit u of one K range -> row group and column group: super rows of SH
+// row groups, in each the column groups in turn, in each of these the row
+// groups, so that the units an XCD runs at a time share operands in its L2.
+__device__ __forceinline__ void dma_unit(int u, int nrg, int ncg, int &rg, int &cg) {
+  constexpr int SH = 8;
+  const int sr = u / (SH * ncg), sh = min(SH, nrg - sr * SH), v = u - sr * SH * ncg;
+  rg = sr * SH + v % sh;
+  cg = v / sh;
+}
+
 // row tile t of row group rg -> matrix and first row
 template <int EPI, int TR, int RTW>
 __device__ __forceinline__ void dma_tile(const GemmArgs &a, int rg, int t, int &m, int &r0) {
@@ -261,19 +271,20 @@ void k_gemm_dma(GemmArgs a) {
   const int wr = wave / WC, wc = wave % WC, li = lane & 15, lq = lane >> 4;
   const int nsb = (a.K / 8 + 15) / 16 * 4;  // sub-blocks of a packed row or column tile
 
-  // Work units in the order (K split, super row of SH row groups, column
-  // group, row group): each XCD (work groups are dealt to the 8 of them round
-  // robin) takes one run of them, so that the units it runs at a time share
-  // their weights and activations in its L2.
-  constexpr int SH = 8;
-  const int nrg = a.n_groups, ncg = a.n_colg, per = nrg * ncg, total = per * a.k_split;
-  const int q8 = total >> 3, r8 = total & 7, xcd = (int)blockIdx.x & 7;
-  const int unit = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + ((int)blockIdx.x >> 3);
-  const int sp = unit / per, u0 = unit - sp * per;
-  const int sr = u0 / (SH * ncg), sh = min(SH, nrg - sr * SH), u1 = u0 - sr * SH * ncg;
-  const int rg = sr * SH + u1 % sh, cg = u1 / sh;
+  // Work units in the order (K split, unit); each XCD (work groups are dealt
+  // to the 8 of them round robin) takes one run of them.  The units of a split
+  // tail follow, a unit's K ranges one after another.
+  const int nrg = a.n_groups, ncg = a.n_colg, per = nrg * ncg;
+  const int total = a.tail_split > 1 ? a.tail_from : per * a.k_split;
+  const int q8 = total >> 3, r8 = total & 7, xcd = (int)blockIdx.x & 7, behind = (int)blockIdx.x - total;
+  const bool tail = EPI == EPI_STORE && behind >= 0;
+  const int unit = tail ? total + behind / a.tail_split
+                        : (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + ((int)blockIdx.x >> 3);
+  const int nks = tail ? a.tail_split : a.k_split, sp = tail ? behind % a.tail_split : unit / per;
+  int rg, cg;
+  dma_unit(tail ? unit : unit - sp * per, nrg, ncg, rg, cg);
   // this split's sub-blocks [g0, g0 + ns), whole k-blocks of 4, in n stages, at least ST (the launcher sees to it)
-  const int kper = (nsb / 4 + a.k_split - 1) / a.k_split * 4;
+  const int kper = (nsb / 4 + nks - 1) / nks * 4;
   const int g0 = sp * kper, ns = min(nsb, g0 + kper) - g0, n = ns / KS;
 
   // this wave's LPW sub-blocks of every stage; tiles past the data have an
@@ -437,9 +448,12 @@ void k_gemm_dma(GemmArgs a) {
       }
     } else {
       // fp32 rows of which there is a multiple of 4, 16-byte aligned
-      const bool add = a.f32_out == F32_RESID;
+      const bool add = a.f32_out == F32_RESID && !tail;
       const int nrow = a.rows[0] + a.rows[1] + a.rows[2];
       float *o = add ? a.resid + (int64_t)col * a.ld_resid : a.splitk_ws + ((int64_t)sp * a.ncols + col) * nrow;
+      if (tail)  // rows and columns of the work-group tile
+        o = a.splitk_ws - rg * TR * 16 +
+            (((int64_t)sp * (per - total) + unit - total) * (TC * 16) + col - cg * TC * 16) * (TR * 16);
 #pragma unroll
       for (int r = 0; r < RTW; ++r) {
         const int row = 16 * (rg * TR + wr * RTW + r) + rr;
@@ -451,6 +465,21 @@ void k_gemm_dma(GemmArgs a) {
       }
     }
   }
+}
+
+// x += the partials of a split tail's unit blockIdx.y, in split order; four
+// rows of one column per thread
+__global__ __launch_bounds__(256) void k_dma_tail_sum(GemmArgs a, int tr, int tc) {
+  const int nu = a.n_groups * a.n_colg - a.tail_from, r4 = tr * 4, i = (int)blockIdx.x * 256 + threadIdx.x;
+  int rg, cg;
+  dma_unit(a.tail_from + (int)blockIdx.y, a.n_groups, a.n_colg, rg, cg);
+  const int lc = i / r4, lr = i % r4 * 4, col = cg * tc * 16 + lc, row = rg * tr * 16 + lr;
+  if (lc >= tc * 16 || col >= a.ncols || row >= a.rows[0]) return;
+  const int64_t slice = (int64_t)nu * tc * tr * 256;
+  const float *p = a.splitk_ws + ((int64_t)blockIdx.y * tc * 16 + lc) * (tr * 16) + lr;
+  f32x4 s = *(const f32x4 *)p;
+  for (int k = 1; k < a.tail_split; ++k) s += *(const f32x4 *)(p + k * slice);
+  *(f32x4 *)(a.resid + (int64_t)col * a.ld_resid + row) += s;
 }
 
 // ---------------------------------------------------------------------------
@@ -483,6 +512,7 @@ struct DmaPlan {
   int shape, k_split;
   bool partial;  // fp32 partials for split_finish
   int n_groups, n_colg;
+  int tail_from, tail_split;
 };
 
 // Takes the shape and K split with the least estimated time.  A CU passes
@@ -490,7 +520,10 @@ struct DmaPlan {
 // sub-block (or, on few columns per row tile, what its MFMAs take), plus ~2.5
 // us to fill and drain its ring; the chip takes as many rounds of work groups
 // as 256 CUs need.  fp32 partials cost their bytes written and read once and
-// a launch.  Measured against the estimate at 64..640 columns of both 7B-shaped
+// a launch.  A residual projection's last round, where it leaves half the CUs
+// idle or more, is cut over K instead into as many ranges as give every CU one:
+// 3584 x 18944 over 14370 columns, 874 units in 4 rounds, takes 3.5 rounds.
+// Measured against the estimate at 64..640 columns of both 7B-shaped
 // models: the chosen shape is within 6 % of the best one.
 inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
   static constexpr DmaShape shapes[] = {
@@ -522,7 +555,22 @@ inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
       if (!found || t < least) {
         found = true;
         least = t;
-        *best = DmaPlan{i, ks, partial, nrg, ncg};
+        *best = DmaPlan{i, ks, partial, nrg, ncg, 0, 1};
+      }
+      const int64_t rest = units % 256;
+      const int ts = resid && !partial && units > 256 && rest && prows % 4 == 0 && a.splitk_ws
+                         ? (int)std::min<int64_t>(DMA_SPLIT_MAX, 256 / rest) : 1;
+      if (ts > 1) {
+        const int tk = (nsb / 4 + ts - 1) / ts * 4;
+        const int64_t tf = ts * rest * sh.tr * sh.tc * 256;
+        if (nsb - (ts - 1) * tk >= sh.fill && tf <= a.splitk_cap && tf <= DMA_SPLIT_FLOATS) {
+          const double each = load > mfma ? load : mfma;
+          t = (double)(units / 256) * (kper * each + 2500.0) + tk * each + 6500.0 + (double)tf * 8.0 / 5000.0;
+          if (t < least) {
+            least = t;
+            *best = DmaPlan{i, ks, partial, nrg, ncg, (int)(units - rest), ts};
+          }
+        }
       }
     }
   }
@@ -531,14 +579,19 @@ inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
 
 template <int DT, int WR, int WC, int RTW, int CTW, int KS, int ST, int EPI>
 hipError_t dma_start(const GemmArgs &g, hipStream_t st) {
-  const dim3 units(g.n_groups * g.n_colg * g.k_split), block(64 * WR * WC);
+  const int n = g.n_groups * g.n_colg;
+  const dim3 units(g.tail_split > 1 ? g.tail_from + (n - g.tail_from) * g.tail_split : n * g.k_split), block(64 * WR * WC);
   // weights that one column group reads alone are not kept in the caches
-  if constexpr (KS > 1)
-    if (g.n_colg == 1) {
-      HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, KS, ST, EPI, true>), units, block, 0, st, g);
-      return hipGetLastError();
-    }
-  HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, KS, ST, EPI, false>), units, block, 0, st, g);
+  bool alone = false;
+  if constexpr (KS > 1) {
+    alone = g.n_colg == 1;
+    if (alone) HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, KS, ST, EPI, true>), units, block, 0, st, g);
+  }
+  if (!alone) HS_LAUNCH((k_gemm_dma<DT, WR, WC, RTW, CTW, KS, ST, EPI, false>), units, block, 0, st, g);
+  const hipError_t e = hipGetLastError();
+  if (EPI != EPI_STORE || e != hipSuccess || g.tail_split <= 1) return e;
+  constexpr int TR = WR * RTW, TC = WC * CTW;
+  HS_LAUNCH(k_dma_tail_sum, dim3((TR * TC * 64 + 255) / 256, n - g.tail_from), dim3(256), 0, st, g, TR, TC);
   return hipGetLastError();
 }
 
@@ -551,6 +604,8 @@ hipError_t gemm_dma(int epi, const GemmArgs &a, int tiles16, int *parts, hipStre
   g.k_split = p.k_split;
   g.n_groups = p.n_groups;
   g.n_colg = p.n_colg;
+  g.tail_from = p.tail_from;
+  g.tail_split = p.tail_split;
   g.f32_out = p.partial ? F32_PARTS : epi == EPI_RESID ? F32_RESID : F32_LOGITS;
   if (p.partial) *parts = p.k_split;
   const bool direct_qkv = epi_qkv(epi) && !p.partial;

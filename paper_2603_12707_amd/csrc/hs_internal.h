@@ -106,6 +106,10 @@ struct GemmArgs {
   // set by the launcher: work groups per column group, and column groups
   int n_groups, n_colg;
   int f32_out;  // k_gemm_dma, EPI_STORE: what the fp32 rows are (F32_*)
+  // k_gemm_dma, F32_RESID: work units from tail_from on are split tail_split
+  // ways over K (1: none), their fp32 partials [split][tail unit][column][row]
+  // of the work-group tile in splitk_ws
+  int tail_from, tail_split;
 };
 enum { F32_LOGITS = 0, F32_PARTS = 1, F32_RESID = 2 };
 

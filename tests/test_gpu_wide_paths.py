@@ -129,3 +129,33 @@ def test_release_keeps_the_other_requests():
     assert free == total and kv.lengths() == [0, 0, 0, 0]
     kv.close()
     pair.gpu.close()
+
+
+def test_residual_split_tail():
+    """8934 rows at d 2048: 280 work-group tiles of O and down, whose last 24 (the last columns) are split eight ways over
+    K.  The short requests in those columns against the oracle, a long one against its own prefill alone (another K order
+    in fp32 moves a stored fp16 value by at most one rounding, 2^-11, at each of the layer's five; 2^-8 covers them)."""
+    cfg = small_cfg(n_layers=1, d_model=2048, n_heads=16, n_kv_heads=16, head_dim=128, ffn_dim=2048, vocab=307,
+                    dtype="f16")
+    import paper_2603_12707_amd as hs
+    shapes = [(300, 6)] * 29 + [(11, 9)] * 3
+    pair = Pair(cfg, max_batch=len(shapes), max_ctx=310)
+    pair.gpu.reserve_rows(sum(a + b for a, b in shapes))
+    ins = [pair.request_inputs(r, a, b) for r, (a, b) in enumerate(shapes)]
+
+    def run(reqs):
+        kv = hs.KVCache(pair.gpu, [a for a, _ in shapes], [310] * len(shapes))
+        logits = torch.empty(len(reqs), cfg["vocab"], dtype=torch.float32, device="cuda")
+        kv.prefill_batch(reqs, torch.cat([ins[r][0] for r in reqs]).cuda(), torch.cat([ins[r][1] for r in reqs]).cuda(),
+                         [shapes[r][1] for r in reqs], None, last_logits=logits)
+        torch.cuda.synchronize()
+        kv.close()
+        return logits.cpu().numpy()
+
+    got = run(list(range(len(shapes))))
+    for r in (29, 30, 31):
+        ref, _ = pair.ora.new_seq(30).prefill(ins[r][0], ins[r][1], None)
+        assert rel_err(got[r], ref) <= LOGIT_TOL, (r, rel_err(got[r], ref))
+    for r in (0, 28):
+        assert rel_err(got[r], run([r])[0]) <= 2.0 ** -8, r
+    pair.gpu.close()
