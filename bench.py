@@ -103,10 +103,9 @@ KIND_NAMES = {
 def kernel_source_hash(kind: str = "gateup") -> str:
     """Hash of the sources that build the kernels of one replayable kind."""
     h = hashlib.sha256()
-    main = "hs_attn.hip" if kind in ("attn", "combine") else "hs_gemm.hip"
-    for rel in ("paper_2603_12707_amd/csrc/" + main, "paper_2603_12707_amd/csrc/hs_device.h",
-                "paper_2603_12707_amd/csrc/hs_internal.h"):
-        with open(os.path.join(ROOT, rel), "rb") as f:
+    own = ("hs_attn.hip",) if kind in ("attn", "combine") else ("hs_gemm.hip", "hs_gemm_dma.h", "hs_gemm_epi.h")
+    for name in own + ("hs_device.h", "hs_internal.h"):
+        with open(os.path.join(ROOT, "paper_2603_12707_amd/csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
 
@@ -528,11 +527,12 @@ def run_workload(name: str, args, ws_cache: dict, stream_gbs: float, headline: b
 # ---------------------------------------------------------------------------
 
 KERNEL_LEGEND = """Template arguments. `k_gemm<dtype, row tiles, column tiles, waves, k-blocks per group, prologue, LDS
-staging, epilogue, packed SwiGLU output, packed activations>` (columns <= 32); `k_gemm_lds<dtype, epilogue, row tiles,
-column tiles>` (LDS-staged, many columns); `k_gemm_ws<dtype, epilogue>` (weight-stationary: gate/up and the LM head at
-129..256 columns); `k_gemm_tile<dtype, row tiles/wave, column tiles/wave, wave rows, wave columns, epilogue>`;
+staging, epilogue, packed SwiGLU output, packed activations>` (columns <= 32); `k_gemm_dma<dtype, wave rows, wave
+columns, row tiles/wave, column tiles/wave, sub-blocks per stage, stages, epilogue, streamed weights>` (16-bit, more
+columns); `k_gemm_lds<dtype, epilogue, row tiles, column tiles>` and `k_gemm_tile<dtype, row tiles/wave, column
+tiles/wave, wave rows, wave columns, epilogue>` (fp32, more columns);
 `k_attn<dtype, head_dim, group, waves, paged cache>` (scalar split attention), `k_attn_mma<...>` (GQA on the matrix
-cores), `k_attn_prefill<...>` (causal prefill); `k_combine<dtype, head_dim, splits unrolled>`. dtype 1 = f16,
+cores), `k_attn_prefill<dtype, head_dim, group, waves, query tiles/wave>` (causal prefill); `k_combine<dtype, head_dim, splits unrolled>`. dtype 1 = f16,
 2 = bf16; prologue 0 = plain activations, 1 = RMSNorm, 2 = attention split combine; epilogue 0 = logits,
 1 = residual, 2 = SwiGLU, 3 = q/k/v + RoPE + KV append, 5 = residual as two fp64 K-split partials. `k_splitk_sum`
 adds the K-split partials of a residual GEMM; `k_rmsnorm<dtype, pending splits>` normalises rows into a workspace
