@@ -7,6 +7,8 @@
 // split along the positions so that short batches still fill the GPU.
 #include "hs_device.h"
 
+#include <cfloat>
+
 namespace hs {
 namespace {
 
@@ -490,6 +492,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 // Slack, in units of the base-2 exponent, by which a column's scores may pass
 // the running maximum before it is raised: exp2(s - m) stays below 2^11.5.
 constexpr float RESCALE_SLACK = 11.5f;
+// From this maximum on, scores are rounded before the maximum is subtracted.
+// Below, one fma of the unrounded product leaves s - m off by at most half an
+// ulp of m, 2^-5 (p up to 2 % more, the same factor in o and l); from here the
+// ulp grows past whole units of the exponent: at 2^34 p of the largest score
+// itself would be 2^+-1024.
+constexpr float ROUND_FROM = 0x1p20f;
 
 template <int DT, int HD, int G, int NW, int QT>
 __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
@@ -580,12 +588,17 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
       dma_1k(vr, (uint32_t)min(4 * lg + i, top) * ROW + (li % CPR) * 16, 0, dst + (KK + i) * 1024);
   };
 
-  float m[QT], l[QT];  // running maximum (base-2 units) and this lane's share of the sum
+  // Running maximum (base-2 units) and this lane's share of the sum.  The
+  // maximum starts at the lowest finite number, which every finite score
+  // raises or equals, so that s - m is a number for s = -inf too.
+  float m[QT], l[QT];
+  bool big[QT];  // some column's |m| >= ROUND_FROM (wave-uniform)
   f32x4 o[QT][8];
 #pragma unroll
   for (int s = 0; s < QT; ++s) {
-    m[s] = -1e30f;
+    m[s] = -FLT_MAX;
     l[s] = 0.f;
+    big[s] = true;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[s][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -646,6 +659,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) o[s][dt] *= corr;
         m[s] = mn;
+        big[s] = __ballot(fabsf(mn) >= ROUND_FROM) != 0;
+      }
+    }
+    float mul[QT], sub[QT];  // p = exp2(score * mul - sub)
+#pragma unroll
+    for (int s = 0; s < QT; ++s) {
+      mul[s] = big[s] ? 1.f : c2;
+      sub[s] = big[s] ? 0.f : m[s];
+      if (big[s]) {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int u = 0; u < KT; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[s][u][i] = sc[s][u][i] * c2 - m[s];
       }
     }
 #pragma unroll
@@ -658,7 +685,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_prefill(AttnArgs a) {
           float p[2];
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[s][u + (x >> 1)][2 * (x & 1) + e], c2, -m[s]));
+            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[s][u + (x >> 1)][2 * (x & 1) + e], mul[s], -sub[s]));
             l[s] += p[e];
           }
           ph[s][x] = pack2<DT>(p[0], p[1]);

@@ -9,18 +9,19 @@ import pytest
 import torch
 
 from helpers import KV_ROW0_TOL, LOGIT_TOL, Pair, rel_err, small_cfg, token_ok
+from workload import synth
 
 pytestmark = pytest.mark.gpu
 TDT = {"f16": torch.float16, "bf16": torch.bfloat16}
 
 
-def _prefill(cfg, shapes, pool):
+def _prefill(cfg, shapes, pool, weights=None):
     """Prefills the requests (n_v, s_text) in one pass; returns the cache, the oracle's sequences and their tokens
     after checking every request's logits, first token and layer-0 K/V rows."""
     import paper_2603_12707_amd as hs
     n = len(shapes)
     caps = [a + b + 4 for a, b in shapes]
-    pair = Pair(cfg, max_batch=n, max_ctx=max(caps))
+    pair = Pair(cfg, max_batch=n, max_ctx=max(caps), weights_cpu=weights)
     pair.gpu.reserve_rows(sum(a + b for a, b in shapes))
     if pool:
         kv = hs.KVPool(pair.gpu, n, 256, sum(-(-c // 256) for c in caps))
@@ -73,6 +74,27 @@ def test_prefill_edges(name, shapes):
     cfg = small_cfg(n_layers=1, d_model=512, n_heads=nh, n_kv_heads=nkv, head_dim=hd, ffn_dim=520, vocab=307,
                     dtype=dtype, qkv_bias=bias, rope_kind=1 if sec else 0, mrope_section=sec or (0, 0, 0))
     pair, kv, _, _ = _prefill(cfg, shapes, pool)
+    assert pair.gpu.status() == 0
+    kv.close()
+    pair.gpu.close()
+
+
+@pytest.mark.parametrize("sign", [1, -1], ids=["high", "low"])
+@pytest.mark.parametrize("dtype,size", [("f16", 250.0), ("f16", 4e4), ("bf16", 250.0), ("bf16", 1e17)])
+@pytest.mark.parametrize("nh,nkv,hd", [(4, 4, 64), (14, 2, 128)])
+def test_prefill_scores_of_any_size(nh, nkv, hd, dtype, size, sign):
+    """q rows that are all `size` and k rows that are all sign * size before RoPE (zero projections, constant biases):
+    scores of either sign up to 1e11 (f16) and 1e36 (bf16), far past where the rounding of a score alone spans many
+    units of its exponent.  The score at distance t is sign * size^2 * sum_i 2 cos(t theta_i): of positive ones the
+    row's own is the largest by 3 %, of negative ones, at these context lengths, one is larger than every other by 2 %
+    of the range, so that the softmax picks one position whatever the order of the sums."""
+    cfg = small_cfg(n_layers=1, d_model=512, n_heads=nh, n_kv_heads=nkv, head_dim=hd, ffn_dim=520, vocab=307,
+                    dtype=dtype, qkv_bias=1)
+    w = synth.make_weights(cfg)
+    for leaf, v in (("q", size), ("k", sign * size)):
+        w["layers.0.w" + leaf].zero_()
+        w["layers.0.b" + leaf].fill_(v)
+    pair, kv, _, _ = _prefill(cfg, [(0, 1), (0, 4), (70, 2), (120, 9)], False, w)
     assert pair.gpu.status() == 0
     kv.close()
     pair.gpu.close()
