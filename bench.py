@@ -103,7 +103,8 @@ KIND_NAMES = {
 def kernel_source_hash(kind: str = "gateup") -> str:
     """Hash of the sources that build the kernels of one replayable kind."""
     h = hashlib.sha256()
-    own = ("hs_attn.hip",) if kind in ("attn", "combine") else ("hs_gemm.hip", "hs_gemm_dma.h", "hs_gemm_epi.h")
+    gemm = ("hs_gemm.hip", "hs_gemm_dma.h", "hs_gemm_plan.h", "hs_gemm_epi.h")
+    own = ("hs_attn.hip",) if kind in ("attn", "combine") else gemm
     for name in own + ("hs_device.h", "hs_internal.h"):
         with open(os.path.join(ROOT, "paper_2603_12707_amd/csrc", name), "rb") as f:
             h.update(f.read())

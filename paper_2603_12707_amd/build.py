@@ -12,6 +12,7 @@ LIB = os.path.join(HERE, "libhs.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("hs_api.cpp", "hs_gemm.hip", "hs_attn.hip", "hs_misc.hip", "hs_handoff.cpp")]
 DEPS = SOURCES + [os.path.join(CSRC, "hs_internal.h"), os.path.join(CSRC, "hs_device.h"),
                   os.path.join(CSRC, "hs_gemm_epi.h"), os.path.join(CSRC, "hs_gemm_dma.h"),
+                  os.path.join(CSRC, "hs_gemm_plan.h"),
                   os.path.join(ROOT, "include", "hs.h")]
 
 FLAGS = [

@@ -1,0 +1,78 @@
+"""The launch rule of the many-column GEMM, on the host: whatever the sizes, the plan it returns covers every row,
+column and K range, fills its ring in each of them and keeps its partials inside the workspace."""
+from __future__ import annotations
+
+import itertools
+import os
+import random
+
+import pytest
+
+import gemm_plan as G
+
+pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"), reason="no HIP headers")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return G.build(str(tmp_path_factory.mktemp("plan") / "plan.so"))
+
+
+def _cases():
+    r = random.Random(7)
+    dims = [8, 64, 128, 136, 256, 640, 688, 1000, 1024, 2048, 3584, 4096, 4608, 11008, 18944]
+    cols = [33, 40, 48, 49, 64, 75, 96, 97, 120, 128, 129, 160, 192, 200, 256, 257, 320, 321, 512, 640, 2048, 3509,
+            8934, 14370, 65536]
+    for epi in G.EPI:
+        for K, n in itertools.product(dims, cols):
+            rows = {"store": (r.choice([1, 17, 301, 1024, 32000, 152064]),), "resid": (r.choice(dims),),
+                    "swiglu": (r.choice(dims),) * 2}.get(epi)
+            if epi == "qkv":
+                hd, nkv = r.choice([64, 128]), r.choice([1, 2, 4, 8, 32])
+                rows = (hd * nkv * r.choice([1, 2, 4, 7, 8]), hd * nkv, hd * nkv)
+            for cap in (0, 4 * n * sum(rows) // 3, 1 << 20, 16 << 20):
+                yield epi, rows, K, n, cap
+
+
+def test_plans_of_all_sizes(lib):
+    seen = set()
+    for epi, rows, K, n, cap in _cases():
+        p = G.plan(lib, epi, rows, K, n, cap)
+        what = (epi, rows, K, n, cap, p)
+        assert p is not None, what
+        tr, tc, fill = G.SHAPES[p.shape]
+        seen.add((p.shape, epi))
+        tiles16 = sum(rows) // 16 if epi == "qkv" else (rows[0] + 15) // 16
+        per_row = tr // 2 if epi == "swiglu" else tr
+        assert (p.n_groups - 1) * per_row < tiles16 <= p.n_groups * per_row, what
+        assert (p.n_colg - 1) * tc * 16 < n <= p.n_colg * tc * 16, what
+        blocks = (K // 8 + 15) // 16  # k-blocks of four sub-blocks
+
+        def ranges(parts):
+            per = -(-blocks // parts) * 4
+            return [min(4 * blocks, (i + 1) * per) - i * per for i in range(parts)]
+        assert min(ranges(p.k_split)) >= fill, what
+        assert p.k_split == 1 or p.partial, what  # split sums go through the workspace
+        out_rows = sum(rows) if epi == "qkv" else rows[0]
+        if p.partial:
+            assert epi in ("resid", "qkv") and out_rows % 4 == 0, what
+            assert p.k_split * n * out_rows <= min(cap, 16 << 20), what
+        if epi == "qkv" and not p.partial:
+            assert p.shape >= 9, what  # the shapes with a q/k/v epilogue of their own
+        if p.tail_split > 1:
+            units = p.n_groups * p.n_colg
+            assert epi == "resid" and p.k_split == 1 and not p.partial, what
+            assert 0 < p.tail_from < units and p.tail_from % 256 == 0, what
+            assert min(ranges(p.tail_split)) >= fill, what
+            tail = units - p.tail_from
+            assert tail * p.tail_split <= 256 and tail * p.tail_split * tr * tc * 256 <= cap, what
+    assert {s for s, _ in seen} == set(range(len(G.SHAPES)))
+
+
+def test_shapes_table(lib):
+    """SHAPES repeats the library's table."""
+    import re
+    with open(os.path.join(G.ROOT, "paper_2603_12707_amd", "csrc", "hs_gemm_plan.h")) as f:
+        rows = re.findall(r"X\((\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (\d+)\)", f.read())
+    got = [(wr * rtw, wc * ctw, ks * st) for _, wr, wc, rtw, ctw, ks, st in (map(int, r) for r in rows)]
+    assert got == G.SHAPES
