@@ -418,6 +418,7 @@ int decode_step_args(hs_model *m, hs_kv *kv, hipStream_t st, Step *out, int *blo
   if (ns > 1 && (int64_t)B * c.n_heads * ns > m->part_entries)
     return fail(HS_E_INVALID, "decode: attention workspace too small");
   *out = Step{m, kv, B, 0, PackedRows{}, kv->d_rope, B, S, ns, st, model_ws(m)};
+  out->ws.splitk_floats = step_splitk_floats(c, B, ns);  // at most what the model holds (n <= max_batch)
   return HS_OK;
 }
 
@@ -620,7 +621,7 @@ int hs_model_create(const hs_config *cfg, const hs_weights *w, int32_t max_batch
     if (ns > 1) entries = std::max(entries, (int64_t)nq * nh * ns);
   }
   m->part_entries = entries;
-  m->splitk_floats = splitk_floats_for(max_batch, rows, std::max(c.d_model, (c.n_heads + 2 * c.n_kv_heads) * c.head_dim));
+  m->splitk_floats = splitk_floats_for(max_batch, rows, splitk_rows(c));
 
   struct Alloc {
     void **p;
@@ -1025,57 +1026,47 @@ extern "C" int hs_decode_step_static(hs_model *m, hs_kv *kv, const int32_t *toke
   if (B <= 0) return fail(HS_E_STATE, "%s: no prefilled request", fn);
   int S, ns;
   kv_split_policy(c, kv->pool, B, kv->max_cap, &S, &ns);
-  // the step's scratch, carved in 256-byte aligned pieces
-  const int64_t b = dtype_bytes(c.dtype), nhd = (int64_t)c.n_heads * c.head_dim;
-  const int64_t qkv_rows = (int64_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim;
-  int64_t splitk_floats = splitk_floats_for(B, B, std::max<int64_t>(c.d_model, qkv_rows));
-  const int64_t entries = ns > 1 ? (int64_t)B * c.n_heads * ns : 1;
-  uint64_t sizes[10] = {(uint64_t)B * c.d_model * 4,
-                              (uint64_t)(B * nhd * b),
-                              (uint64_t)(act_elems(B, nhd) * b),
-                              (uint64_t)(act_elems(B, c.ffn_dim) * b),
-                              (uint64_t)(act_elems(B, c.d_model) * b),
-                              (uint64_t)splitk_floats * 4,
-                              (uint64_t)entries * c.head_dim * 4,
-                              (uint64_t)entries * 2 * 4,
-                              (m->w.lm_head && !logits) ? (uint64_t)B * c.vocab * 4 : 0u,
-                              0u};
-  uint64_t offs[10], total = 0;
-  for (int i = 0; i < 10; ++i) total += (sizes[i] + 255) / 256 * 256;
-  // a step whose whole K-split workspace does not fit takes fewer splits
-  // (never less than the deferred sums of a narrow batch need)
-  const uint64_t least = std::min<uint64_t>(sizes[5], (uint64_t)SPLITK_MAX * B * c.d_model * 4);
-  if (total > HS_STATIC_SCRATCH_BYTES) {
-    const uint64_t over = (total - HS_STATIC_SCRATCH_BYTES + 255) / 256 * 256;
-    sizes[5] = sizes[5] > over + least ? sizes[5] - over : least;
-    splitk_floats = (int64_t)(sizes[5] / 4);
-  }
-  total = 0;
-  for (int i = 0; i < 10; ++i) {
-    offs[i] = total;
-    total += (sizes[i] + 255) / 256 * 256;
-  }
-  if (total > HS_STATIC_SCRATCH_BYTES)
+  const StepScratch sz = step_scratch(c, B, ns);
+  const uint64_t own_logits = m->w.lm_head && !logits ? sz.logits : 0;
+  const uint64_t least = sz.layers() + own_logits + whole256(SPLITK_MAX * B * splitk_rows(c) * 4);
+  if (least > HS_STATIC_SCRATCH_BYTES)
     return fail(HS_E_INVALID, "%s: this step needs %llu bytes of scratch, the static array holds %llu", fn,
-                (unsigned long long)total, (unsigned long long)HS_STATIC_SCRATCH_BYTES);
+                (unsigned long long)least, (unsigned long long)HS_STATIC_SCRATCH_BYTES);
+  const int64_t splitk_floats = step_splitk_floats(c, B, ns);
   void *base = nullptr;
   int rc = scratch_ptr(dev, &base);
   if (rc) return rc;
+  // The residual stream and the normalised rows first; then the rest of the
+  // layers' scratch, whose place the logits take: the LM head runs after the
+  // last layer, and its norm is the last reader of K-split partials.
   char *p = (char *)base;
-  StepWs ws{(float *)(p + offs[0]), p + offs[1], p + offs[2], p + offs[3], p + offs[4], (float *)(p + offs[5]),
-            splitk_floats, (float *)(p + offs[6]), (float *)(p + offs[7]),
-            sizes[8] ? (float *)(p + offs[8]) : nullptr};
+  auto carve = [&](uint64_t bytes) {
+    char *at = p;
+    p += bytes;
+    return at;
+  };
+  StepWs ws{};
+  ws.x = (float *)carve(sz.x);
+  ws.hnorm = carve(sz.hnorm);
+  ws.logits = own_logits ? (float *)p : nullptr;
+  ws.q = carve(sz.q);
+  ws.attn = carve(sz.attn);
+  ws.act = carve(sz.act);
+  ws.part_o = (float *)carve(sz.part_o);
+  ws.part_ml = (float *)carve(sz.part_ml);
+  ws.splitk = (float *)carve(whole256(splitk_floats * 4));
+  ws.splitk_floats = splitk_floats;
   // The array keeps whatever the last call left.  The activations read in the
   // packed layout are read in whole k-blocks of 128 elements, past K up to
   // the block's end, against weight rows that are zero there: those elements
   // must hold finite values, so a K that is not a multiple of 128 has its
   // buffer cleared first.  Everything else a step reads it writes first.
   hipStream_t st = (hipStream_t)stream;
-  const int64_t ks[3] = {nhd, c.ffn_dim, c.d_model};
+  const int64_t ks[3] = {(int64_t)c.n_heads * c.head_dim, c.ffn_dim, c.d_model};
   void *bufs[3] = {ws.attn, ws.act, ws.hnorm};
+  const uint64_t bytes[3] = {sz.attn, sz.act, sz.hnorm};
   for (int i = 0; i < 3; ++i)
-    if (ks[i] % 128 && gemm_x_packed(c.dtype, B, (int)ks[i]))
-      HIP_TRY(launch_zero(bufs[i], sizes[2 + i], st));
+    if (ks[i] % 128 && gemm_x_packed(c.dtype, B, (int)ks[i])) HIP_TRY(launch_zero(bufs[i], bytes[i], st));
   return decode_impl(m, kv, tokens_in, tokens_out, logits, hidden_out, stream, &ws, fn);
 }
 

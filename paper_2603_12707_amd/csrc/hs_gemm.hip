@@ -1295,10 +1295,6 @@ hipError_t launch_resid_pending(const double *part, int k_split, int ncols, int 
   return hipGetLastError();
 }
 
-int64_t act_elems(int64_t rows, int64_t K) {
-  return (std::max<int64_t>(rows, 32) + 15) / 16 * 16 * ((K + 127) / 128 * 128);
-}
-
 hipError_t launch_gemm(int dtype, int pro, int epi, const GemmArgs &a, hipStream_t st) {
   if (a.ncols <= 0 || a.rows[0] <= 0) return hipSuccess;
   switch (dtype) {

@@ -131,6 +131,43 @@ inline int64_t splitk_floats_for(int64_t max_batch, int64_t rows, int64_t widest
 #ifndef HS_STATIC_SCRATCH_BYTES
 #define HS_STATIC_SCRATCH_BYTES (64ull << 20)
 #endif
+// elements an activation buffer of `rows` rows of K needs, the packed layout
+// included
+inline int64_t act_elems(int64_t rows, int64_t K) {
+  return ((rows > 32 ? rows : 32) + 15) / 16 * 16 * ((K + 127) / 128 * 128);
+}
+// rows of the widest GEMM whose K split leaves partials
+inline int64_t splitk_rows(const hs_config &c) {
+  const int64_t qkv = (int64_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim;
+  return qkv > c.d_model ? qkv : c.d_model;
+}
+// The scratch of one decode step over n columns with n_split attention
+// splits, K-split partials apart: bytes, each piece in whole 256s.
+struct StepScratch {
+  uint64_t x, q, attn, act, hnorm, part_o, part_ml, logits;
+  uint64_t layers() const { return x + q + attn + act + hnorm + part_o + part_ml; }  // all but the logits
+};
+inline uint64_t whole256(int64_t bytes) { return ((uint64_t)bytes + 255) / 256 * 256; }
+inline StepScratch step_scratch(const hs_config &c, int64_t n, int n_split) {
+  const int64_t b = c.dtype == HS_F32 ? 4 : 2, nhd = (int64_t)c.n_heads * c.head_dim;
+  const int64_t entries = n_split > 1 ? n * c.n_heads * n_split : 1;
+  return StepScratch{whole256(n * c.d_model * 4),       whole256(n * nhd * b),
+                     whole256(act_elems(n, nhd) * b),   whole256(act_elems(n, c.ffn_dim) * b),
+                     whole256(act_elems(n, c.d_model) * b), whole256(entries * c.head_dim * 4),
+                     whole256(entries * 2 * 4),         whole256(n * c.vocab * 4)};
+}
+// Floats of K-split partials that decode steps over n columns split by, the
+// same in the model's workspace and in the static array, so that both run the
+// same kernels: what splitk_floats_for asks for, or SPLITK_MAX splits of the
+// widest GEMM where the static array holds only those beside the layers'
+// scratch (the logits take the layers' place).
+inline int64_t step_splitk_floats(const hs_config &c, int64_t n, int n_split) {
+  const int64_t rows = splitk_rows(c), all = splitk_floats_for(n, n, rows), few = (int64_t)SPLITK_MAX * n * rows;
+  const uint64_t layers = step_scratch(c, n, n_split).layers();
+  const bool only_few = layers + whole256(all * 4) > HS_STATIC_SCRATCH_BYTES &&
+                        layers + whole256(few * 4) <= HS_STATIC_SCRATCH_BYTES;
+  return only_few ? few : all;
+}
 // the attention combine runs in the projection's prologue for at most this
 // many splits (and activations that fit the prologue's LDS copy)
 constexpr int COMBINE_FUSE_SPLITS = 8;
@@ -185,9 +222,6 @@ int resid_defer_splits(int dtype, int ncols, int K, int d_model, int64_t cap);
 // summed in split order (the sum k_rmsnorm applies), for a pass that ends
 // without a normalisation
 hipError_t launch_resid_pending(const double *part, int k_split, int ncols, int rows, float *x, hipStream_t st);
-// elements an activation buffer of `rows` rows of K needs, the packed layout
-// of up to 32 columns included
-int64_t act_elems(int64_t rows, int64_t K);
 // whether launch_gemm takes PRO_COMBINE for these shapes
 bool gemm_combine_fusable(int dtype, int ncols, int K, int n_heads, int n_split);
 hipError_t launch_pack(int dtype, const void *src, int64_t rows, int64_t cols, void *dst, int pair_hd,

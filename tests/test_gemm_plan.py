@@ -69,6 +69,29 @@ def test_plans_of_all_sizes(lib):
     assert {s for s, _ in seen} == set(range(len(G.SHAPES)))
 
 
+def test_step_scratch_of_all_sizes(lib):
+    """A decode step's K-split partials: the static array holds them beside the layers' scratch whenever it accepts the
+    step, they hold SPLITK_MAX splits of the widest GEMM, and the q/k/v, O and down plans find room."""
+    import ctypes
+    r = random.Random(3)
+    static, few_seen = 64 << 20, 0
+    for _ in range(4000):
+        hd, nkv, g = r.choice([64, 128]), r.choice([1, 2, 4, 8, 32]), r.choice([1, 2, 4, 7, 8])
+        d, F = 8 * r.randint(1, 700), 8 * r.randint(1, 2500)
+        V, n, ns = r.choice([301, 32000, 152064]), r.randint(1, 700), r.choice([1, 1, 2, 8, 40])
+        out = (ctypes.c_int64 * 4)()
+        lib.plan_step(d, nkv * g, nkv, hd, F, V, r.randint(0, 2), n, ns, out)
+        layers, logits, few, floats = out
+        what = (d, nkv * g, nkv, hd, F, V, n, ns, list(out))
+        rows = max(d, (g + 2) * nkv * hd)
+        assert few == -(-16 * n * rows // 256) * 256 and floats >= 4 * n * rows, what
+        assert floats <= max(4 * n * rows, min(8 * n * rows, 16 << 20)), what
+        if layers + few <= static:  # accepted, with the caller's logits or (logits in the layers' place) its own
+            assert layers + -(-4 * floats // 256) * 256 <= static, what
+        few_seen += floats < min(8 * n * rows, 16 << 20)
+    assert few_seen > 50
+
+
 def test_shapes_table(lib):
     """SHAPES repeats the library's table."""
     import re

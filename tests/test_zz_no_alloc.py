@@ -75,6 +75,43 @@ def test_static_scratch_step_equals_decode_step_on_consecutive_calls():
     _compare(cfg, [30, 0, 11], [4, 20, 1], 3, False)
 
 
+@pytest.mark.parametrize("batch,vocab,with_logits", [(75, 301, True), (200, 301, False), (200, 73792, False),
+                                                     (200, 73792, True)],
+                         ids=["75", "200", "200_nearly_full", "200_wide_vocab"])
+def test_static_scratch_step_over_many_columns(batch, vocab, with_logits):
+    """More than 32 columns, where the GEMMs split K (down, 4096 inputs over 200 columns, in eight): the split follows
+    the configuration and the batch alone, also where the step's logits leave the array room for half the partials."""
+    import paper_2603_12707_amd as hs
+    from workload import synth
+    cfg = small_cfg(n_layers=2, d_model=1024, n_heads=4, n_kv_heads=4, head_dim=64, ffn_dim=4096, vocab=vocab,
+                    dtype="f16")
+    model = hs.Model(cfg, synth.make_weights(cfg, device="cuda"), max_batch=batch, max_ctx=40)
+    lens, caps = [1 + (7 * r) % 29 for r in range(batch)], [40] * batch
+    elems = batch * hs.hs_kv_bytes(cfg, 0, 40)[0] // 2
+    rows = synth.normal(5, "kv", (elems,), 1.0, "f16", device="cuda")
+    kvs = [hs.KVCache(model, [0] * batch, caps, rows.clone().view(torch.uint8)) for _ in range(2)]
+    tok = synth.uniform_int(5, "tok", batch, 0, vocab - 1, device="cuda")
+    out = []
+    for kv, step in zip(kvs, ("decode", "decode_static")):
+        for r, n in enumerate(lens):
+            kv.set_length(r, n, n)
+        t, o = tok.clone(), torch.empty_like(tok)
+        hidden = torch.empty(batch, cfg["d_model"], device="cuda")
+        logits = torch.zeros(batch, vocab, device="cuda") if with_logits else None
+        res = []
+        for _ in range(3):
+            getattr(kv, step)(t, o, logits, hidden)
+            res += [o.clone(), hidden.clone()] + ([logits.clone()] if with_logits else [])
+            t, o = o, t
+        torch.cuda.synchronize()
+        out.append(res)
+        kv.close()
+    for i, (a, b) in enumerate(zip(*out)):
+        assert torch.equal(a, b), i
+    assert model.status() == 0
+    model.close()
+
+
 def test_static_scratch_step_refuses_a_step_that_does_not_fit():
     import paper_2603_12707_amd as hs
     cfg = small_cfg(n_layers=1, d_model=64, n_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=128, vocab=300_000,
