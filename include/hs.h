@@ -146,8 +146,11 @@ int hs_pack_matrix_heads(int32_t dtype, const void *src, int64_t rows, int64_t c
 /* Validates cfg, records the caller-owned weight pointers (they must outlive
  * the model) and allocates the workspaces for decode batches of up to
  * max_batch requests and requests of up to max_ctx positions (prefill rows,
- * capacities and RoPE position ids are all < max_ctx).  Uses the current
- * HIP device. */
+ * capacities and RoPE position ids are all < max_ctx).  Of these the partials
+ * of GEMMs that split K take min(8 R W, 2^24) floats, or 4 max_batch W where
+ * that is more (R = max(max_batch, max_ctx) rows, W the larger of d_model and
+ * the q|k|v rows): 64 MiB in a 7B-shaped model from a few hundred rows on.
+ * Uses the current HIP device. */
 int hs_model_create(const hs_config *cfg, const hs_weights *w, int32_t max_batch, int32_t max_ctx, hs_model **out);
 int hs_model_free(hs_model *m);
 
@@ -285,9 +288,9 @@ int hs_prefill_batch(hs_model *m, hs_kv *kv, int32_t n, const int32_t *reqs, con
                      int32_t *first_tokens, hs_stream_t stream);
 
 /* Grows the model's row workspaces (residual stream, q, attention and SwiGLU
- * outputs, normalised rows) to hold `rows` packed prefill rows, so that
- * hs_prefill_batch packs more requests per pass; never shrinks them.  It
- * allocates, and waits for the device to go idle before freeing the old
+ * outputs, normalised rows, K-split partials) to hold `rows` packed prefill
+ * rows, so that hs_prefill_batch packs more requests per pass; never shrinks
+ * them.  It allocates, and waits for the device to go idle before freeing the old
  * buffers: call it outside any stream capture and not from a serving loop.
  * When it grows them, a HIP graph captured earlier from this model's decode
  * steps still holds the freed buffers' addresses: capture it again before

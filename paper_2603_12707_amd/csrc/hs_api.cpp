@@ -902,13 +902,18 @@ int hs_model_reserve_rows(hs_model *m, int64_t rows) {
   if (rows <= m->rows) return HS_OK;
   const hs_config &c = m->cfg;
   const int b = dtype_bytes(c.dtype), nhd = c.n_heads * c.head_dim;
-  constexpr int NB = 6;
+  const int64_t splitk = std::max(m->splitk_floats, splitk_floats_for(m->max_batch, rows, splitk_rows(c)));
+  constexpr int NB = 7;
   void *fresh[NB] = {};
-  const size_t bytes[NB] = {(size_t)rows * c.d_model * 4, (size_t)rows * nhd * b, (size_t)act_elems(rows, nhd) * b,
-                           (size_t)act_elems(rows, c.ffn_dim) * b, (size_t)act_elems(rows, c.d_model) * b,
-                            (size_t)prefill_groups_max(rows) * sizeof(PrefillGroup)};
+  const size_t bytes[NB] = {(size_t)rows * c.d_model * 4,
+                            (size_t)rows * nhd * b,
+                            (size_t)act_elems(rows, nhd) * b,
+                            (size_t)act_elems(rows, c.ffn_dim) * b,
+                            (size_t)act_elems(rows, c.d_model) * b,
+                            (size_t)prefill_groups_max(rows) * sizeof(PrefillGroup),
+                            splitk > m->splitk_floats ? (size_t)splitk * 4 : 0};
   for (int i = 0; i < NB; ++i)
-    if (hipMalloc(&fresh[i], bytes[i]) != hipSuccess) {
+    if (bytes[i] && hipMalloc(&fresh[i], bytes[i]) != hipSuccess) {
       for (void *p : fresh)
         if (p) (void)hipFree(p);
       return fail(HS_E_DEVICE, "hs_model_reserve_rows: hipMalloc of %zu bytes failed", bytes[i]);
@@ -917,14 +922,17 @@ int hs_model_reserve_rows(hs_model *m, int64_t rows) {
   // activations start cleared (as in hs_model_create)
   if (hipDeviceSynchronize() != hipSuccess || hipMemset(fresh[2], 0, bytes[2]) != hipSuccess ||
       hipMemset(fresh[3], 0, bytes[3]) != hipSuccess || hipMemset(fresh[4], 0, bytes[4]) != hipSuccess) {
-    for (void *p : fresh) (void)hipFree(p);
+    for (void *p : fresh)
+      if (p) (void)hipFree(p);
     return fail(HS_E_DEVICE, "hs_model_reserve_rows: device synchronisation failed");
   }
-  void **slots[NB] = {(void **)&m->x, &m->q, &m->attn, &m->act, &m->hnorm, (void **)&m->pk_order};
+  void **slots[NB] = {(void **)&m->x, &m->q, &m->attn, &m->act, &m->hnorm, (void **)&m->pk_order, (void **)&m->splitk};
   for (int i = 0; i < NB; ++i) {
+    if (!fresh[i]) continue;
     (void)hipFree(*slots[i]);
     *slots[i] = fresh[i];
   }
+  m->splitk_floats = splitk;
   m->rows = rows;
   return HS_OK;
 }

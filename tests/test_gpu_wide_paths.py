@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import KV_ROW0_TOL, LOGIT_TOL, Pair, rel_err, small_cfg, token_ok
+from helpers import KV_ROW0_TOL, LOGIT_TOL, Pair, rel_err, small_cfg, to_device, token_ok
 from workload import synth
 
 pytestmark = pytest.mark.gpu
@@ -98,6 +98,28 @@ def test_prefill_scores_of_any_size(nh, nkv, hd, dtype, size, sign):
     assert pair.gpu.status() == 0
     kv.close()
     pair.gpu.close()
+
+
+def test_reserved_rows_run_as_created_ones():
+    """Eight requests of 64 rows in one pass: a model whose rows were reserved after its creation gives, bit for bit,
+    what one created for as many rows gives (the down projection splits K by the size of the workspace)."""
+    import paper_2603_12707_amd as hs
+    cfg = small_cfg(n_layers=1, d_model=1024, n_heads=8, n_kv_heads=8, head_dim=128, ffn_dim=4096, vocab=307,
+                    dtype="f16")
+    w = to_device(synth.make_weights(cfg))
+    ids = torch.cat([synth.text_ids(cfg, r, 64) for r in range(8)]).cuda()
+    got = []
+    for max_ctx in (512, 64):
+        model = hs.Model(cfg, w, max_batch=8, max_ctx=max_ctx)
+        model.reserve_rows(512)
+        kv = hs.KVCache(model, [0] * 8, [64] * 8)
+        logits = torch.empty(8, cfg["vocab"], dtype=torch.float32, device="cuda")
+        kv.prefill_batch(list(range(8)), None, ids, [64] * 8, None, last_logits=logits)
+        torch.cuda.synchronize()
+        got.append(logits)
+        kv.close()
+        model.close()
+    assert torch.equal(got[0], got[1])
 
 
 @pytest.mark.parametrize("batch", [33, 65, 129])
