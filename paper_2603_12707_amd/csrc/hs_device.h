@@ -218,15 +218,22 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lds_byte *)p; }
 // Lane l's 16 bytes at voff + soff of the range go to LDS byte lds + 16 l
 // (rsrc, soff, lds wave-uniform).  No destination registers; the wait is the
-// caller's (dma_sync).
+// caller's (dma_sync).  m0 is no clobber: the compiler reserves it, keeps
+// nothing in it and sets it before each use of its own.  Nor does the compiler
+// put wait states in front of inline asm: an SGPR operand written by a vector
+// instruction (v_readfirstlane) must be five old when the load reads it, of
+// which the two instructions here are two.  A test counts them in the built
+// code (supplying all five here cost prefill 1-2 %).
 __device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
-               "s"(rsrc), "s"(soff));
+               "s"(rsrc), "s"(soff)
+               : "memory");
 }
 // non-temporal: data read once per launch (weights under a single column group)
 __device__ __forceinline__ void dma_1k_stream(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff),
-               "s"(rsrc), "s"(soff));
+               "s"(rsrc), "s"(soff)
+               : "memory");
 }
 // at most N of this wave's loads still in flight, its LDS reads done, then a
 // work-group barrier
