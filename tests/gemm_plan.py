@@ -6,6 +6,8 @@ import ctypes
 import os
 import subprocess
 
+from workload import configs
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 EPI = {"store": 0, "resid": 1, "swiglu": 2, "qkv": 3}
 # row tiles, column tiles and ring depth (sub-blocks of 32 elements of K) of the shapes
@@ -38,3 +40,32 @@ def gemms(cfg: dict) -> dict:
     q, k = cfg["n_heads"] * cfg["head_dim"], cfg["n_kv_heads"] * cfg["head_dim"]
     return {"qkv": ("qkv", (q, k, k), d), "o": ("resid", (d,), q), "gateup": ("swiglu", (F, F), d),
             "down": ("resid", (d,), F), "head": ("store", (cfg["vocab"],), d)}
+
+
+def step_floats(lib, cfg: dict, n: int) -> int:
+    """Floats of K-split partials of a decode step over n columns (attention in one split)."""
+    out = (ctypes.c_int64 * 4)()
+    lib.plan_step(*(cfg[k] for k in ("d_model", "n_heads", "n_kv_heads", "head_dim", "ffn_dim", "vocab")),
+                  configs.DTYPE_CODE[cfg["dtype"]], n, 1, out)
+    return out[3]
+
+
+def step_kinds(lib, cfg: dict, n: int) -> dict:
+    """projection -> (shape, how it stores, whether one column group covers the batch) of a decode step over n columns"""
+    kinds = {}
+    for g, (epi, rows, K) in gemms(cfg).items():
+        p = plan(lib, epi, rows, K, n, step_floats(lib, cfg, n))
+        kinds[g] = (p.shape, epi + ("_part" if p.partial else "_tail" if p.tail_split > 1 else ""), p.n_colg == 1)
+    return kinds
+
+
+# Decode batches of one layer and the LM head that run, between them, every (shape, store, column groups) that the rule
+# chooses for the two 7B-shaped models over batches below 4100 (a pooled cache holds up to 4096 requests).
+SHAPE_CASES = {
+    "llava7b_b1": [33, 65, 123, 129, 257, 513, 641, 903, 1540, 2063, 2247, 2821],
+    "qwen7b_b16": [33, 65, 113, 129, 150, 304, 560, 641, 1253, 1414, 2884],
+}
+
+
+def shape_cfg(model: str) -> dict:
+    return configs.get(model, n_layers=1)

@@ -92,6 +92,23 @@ def test_step_scratch_of_all_sizes(lib):
     assert few_seen > 50
 
 
+def test_shape_cases_run_every_kind(lib):
+    """The decode batches that the GPU tests compare with the oracle (test_gpu_gemm_shapes.py) reach whatever the rule
+    chooses over the batches below 4100."""
+    want, got = {}, set()
+    for model, batches in G.SHAPE_CASES.items():
+        cfg = G.shape_cfg(model)
+        for n in itertools.chain(range(33, 700), range(700, 4100, 7)):
+            for g, kind in G.step_kinds(lib, cfg, n).items():
+                want.setdefault(kind, (model, g, n))
+        for n in batches:
+            got |= set(G.step_kinds(lib, cfg, n).values())
+    missing = {k: w for k, w in want.items() if k not in got}
+    assert not missing, missing
+    assert {s for s, kind, _ in got if kind == "swiglu"} >= {0, 2, 3, 5, 6, 8, 10, 12}
+    assert {s for s, _, _ in got} == set(range(len(G.SHAPES)))
+
+
 def test_shapes_table(lib):
     """SHAPES repeats the library's table."""
     import re
