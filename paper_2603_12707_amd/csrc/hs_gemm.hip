@@ -657,22 +657,21 @@ __global__ __launch_bounds__(64 * NW) void k_gemm(GemmArgs a) {
   }
 }
 
-// Many columns (B > 32, and prefill): Y = X W^T as a tiled GEMM.  A work group
-// owns WR x RTW row tiles and WC x CTW column tiles; wave (wr, wc) computes
-// its RTW x CTW output tiles over the whole K, so there is no reduction
-// between waves and every weight operand feeds CTW MFMAs and every activation
-// operand RTW.  Operands go straight from global memory into MFMA registers,
-// one 32-element k step (a 1 KB weight sub-block per row tile, 16 bytes per
-// lane per column tile) at a time, through a ring of two steps.  SwiGLU work
-// groups hold gate tiles in their first RTW / 2 rows of each wave and the
-// matching up tiles in the rest.  Activations are plain rows of the storage
-// dtype (normalised once by k_rmsnorm when the projection has a norm).
-// Accumulation is fp32 over the whole K.
-template <int DT, int RTW, int CTW, int WR, int WC, int EPI>
+// Many columns (B > 32, and prefill) in fp32 storage (16-bit storage runs
+// k_gemm_dma): Y = X W^T as a tiled GEMM.  A work group owns WR x RTW row tiles
+// and WC x CTW column tiles; wave (wr, wc) computes its RTW x CTW output tiles
+// over the whole K, so there is no reduction between waves and every weight
+// operand feeds CTW MFMAs and every activation operand RTW.  Operands go
+// straight from global memory into MFMA registers, one 16-element k step (a
+// 1 KB weight sub-block per row tile, 16 bytes per lane per column tile) at a
+// time, through a ring of two steps.  SwiGLU work groups hold gate tiles in
+// their first RTW / 2 rows of each wave and the matching up tiles in the rest.
+// Activations are plain rows (normalised once by k_rmsnorm when the projection
+// has a norm).  Accumulation is fp32 over the whole K.
+template <int RTW, int CTW, int WR, int WC, int EPI>
 __global__ __launch_bounds__(64 * WR * WC) void k_gemm_tile(GemmArgs a) {
-  using S = typename Ty<DT>::S;
-  constexpr int CE = Ty<DT>::CE;
-  constexpr int SB = (int)sizeof(S);
+  constexpr int DT = HS_F32, CE = Ty<DT>::CE, SB = 4;
+  using S = float;
   constexpr int D = 2;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -694,7 +693,7 @@ __global__ __launch_bounds__(64 * WR * WC) void k_gemm_tile(GemmArgs a) {
       constexpr int H = RTW / 2;
       mat[r] = r < H ? 0 : 1;
       row0[r] = 16 * ((rg * WR + wr) * H + (r % H));
-    } else if constexpr (epi_qkv(EPI)) {
+    } else if constexpr (EPI == EPI_QKV) {
       const int tq = a.n_heads * a.head_dim / 16, tk = a.n_kv * a.head_dim / 16;
       int m = 0, t = (rg * WR + wr) * RTW + r;
       if (t >= tq) {
@@ -763,13 +762,13 @@ __global__ __launch_bounds__(64 * WR * WC) void k_gemm_tile(GemmArgs a) {
         const f32x4 v2[2] = {acc[r][c], acc[r + H][c]};
         gemm_epilogue<DT, EPI_SWIGLU, 2>(a, m2, r2, v2, col, rr);
       }
-    } else if constexpr (epi_qkv(EPI)) {
+    } else if constexpr (EPI == EPI_QKV) {
 #pragma unroll
       for (int r = 0; r < RTW; ++r) {
         QkvIn<1> in;
-        qkv_fetch_ids<DT, 1, EPI == EPI_QKV_PAGED>(a, &mat[r], &row0[r], col, rr, true, in);
+        qkv_fetch_ids<DT, 1, false>(a, &mat[r], &row0[r], col, rr, true, in);
         qkv_fetch_tab<DT, 1>(a, &mat[r], &row0[r], rr, true, in);
-        qkv_store<DT, 1, EPI == EPI_QKV_PAGED>(a, &mat[r], &row0[r], &acc[r][c], col, rr, in);
+        qkv_store<DT, 1, false>(a, &mat[r], &row0[r], &acc[r][c], col, rr, in);
       }
     } else {
 #pragma unroll
@@ -778,21 +777,20 @@ __global__ __launch_bounds__(64 * WR * WC) void k_gemm_tile(GemmArgs a) {
   }
 }
 
-// Many columns (prefill rows, large batches) with both operands shared
-// through LDS: a work group of 8 waves (4 x 2) owns RTG row tiles (SwiGLU:
+// Many columns in fp32 storage (prefill rows, large batches) with both operands
+// shared through LDS: a work group of 8 waves (4 x 2) owns RTG row tiles (SwiGLU:
 // RTG/2 gate and the RTG/2 matching up tiles) by CTG column tiles, each wave
-// RTG/4 x CTG/2 of them.  K advances in stages of two 32-element sub-blocks:
+// RTG/4 x CTG/2 of them.  K advances in stages of two 16-element sub-blocks:
 // the stage's weight sub-blocks (1 KB each, contiguous in the packed layout)
 // and activation sub-blocks are staged in LDS in MFMA operand order, and each
 // wave reads the operands of its output tiles from there (16 B per lane,
 // conflict free).  Global loads run two stages ahead through registers, LDS
 // is double buffered.  fp32 accumulation.
 constexpr int LG_NW = 8;
-template <int DT, int EPI, int RTG, int CTG>
+template <int EPI, int RTG, int CTG>
 __global__ __launch_bounds__(64 * LG_NW) void k_gemm_lds(GemmArgs a) {
-  using S = typename Ty<DT>::S;
-  constexpr int CE = Ty<DT>::CE;
-  constexpr int SB = (int)sizeof(S);
+  constexpr int DT = HS_F32, CE = Ty<DT>::CE, SB = 4;
+  using S = float;
   constexpr int RTW = RTG / 4, CTW = CTG / 2;        // tiles per wave
   constexpr int WSUB = RTG * 2, XSUB = CTG * 2;      // 1 KB sub-blocks per stage
   constexpr int WPT = WSUB / LG_NW, XPT = XSUB / LG_NW;  // of them moved per thread
@@ -816,7 +814,7 @@ __global__ __launch_bounds__(64 * LG_NW) void k_gemm_lds(GemmArgs a) {
     rg = (slot / nu) * 8 + ((int)blockIdx.x & 7);
     if (rg >= a.n_groups) return;
   }
-  // this work group's K range, in 32-element sub-blocks [g_begin, g_end)
+  // this work group's K range, in 16-element sub-blocks [g_begin, g_end)
   const int kb_split = (nkb + nks - 1) / nks;
   const int g_begin = ks * kb_split * 4, g_end = min(nsb, (ks + 1) * kb_split * 4);
   const int nstage = g_end > g_begin ? (g_end - g_begin + 1) / 2 : 0;
@@ -827,7 +825,7 @@ __global__ __launch_bounds__(64 * LG_NW) void k_gemm_lds(GemmArgs a) {
       const int w = t / RTW, k = t % RTW;
       m = k < H ? 0 : 1;
       r0 = 16 * (rg * (RTG / 2) + w * H + k % H);
-    } else if constexpr (epi_qkv(EPI)) {
+    } else if constexpr (EPI == EPI_QKV) {
       const int tq = a.n_heads * a.head_dim / 16, tk = a.n_kv * a.head_dim / 16;
       int mm = 0, u = rg * RTG + t;
       if (u >= tq) {
@@ -940,7 +938,7 @@ __global__ __launch_bounds__(64 * LG_NW) void k_gemm_lds(GemmArgs a) {
         const f32x4 v2[2] = {acc[r][c], acc[r + H][c]};
         gemm_epilogue<DT, EPI_SWIGLU, 2>(a, m2, r2, v2, col, rr);
       }
-    } else if ((EPI == EPI_RESID || epi_qkv(EPI)) && nks > 1) {
+    } else if ((EPI == EPI_RESID || EPI == EPI_QKV) && nks > 1) {
       // K split: this split's fp32 partial over the output rows (q/k/v:
       // the q, k and v rows in turn), finished by a second kernel
       const int prows = split_rows(a, EPI);
@@ -952,13 +950,13 @@ __global__ __launch_bounds__(64 * LG_NW) void k_gemm_lds(GemmArgs a) {
           const int row = 16 * (rg * RTG + wr * RTW + r) + rr + e;
           if (row < prows) o[row] = acc[r][c][e];
         }
-    } else if constexpr (epi_qkv(EPI)) {
+    } else if constexpr (EPI == EPI_QKV) {
 #pragma unroll
       for (int r = 0; r < RTW; ++r) {
         QkvIn<1> in;
-        qkv_fetch_ids<DT, 1, EPI == EPI_QKV_PAGED>(a, &mat[r], &row0[r], col, rr, true, in);
+        qkv_fetch_ids<DT, 1, false>(a, &mat[r], &row0[r], col, rr, true, in);
         qkv_fetch_tab<DT, 1>(a, &mat[r], &row0[r], rr, true, in);
-        qkv_store<DT, 1, EPI == EPI_QKV_PAGED>(a, &mat[r], &row0[r], &acc[r][c], col, rr, in);
+        qkv_store<DT, 1, false>(a, &mat[r], &row0[r], &acc[r][c], col, rr, in);
       }
     } else {
 #pragma unroll
@@ -1086,14 +1084,14 @@ hipError_t gemm_global_r(const GemmArgs &p, int tiles16, hipStream_t st) {
 
 // Tiled GEMM launch: work-group tiles of WR*RTW row tiles by WC*CTW column
 // tiles (SwiGLU: RTW/2 gate and RTW/2 up tiles per wave).
-template <int DT, int RTW, int CTW, int WR, int WC, int EPI>
+template <int RTW, int CTW, int WR, int WC, int EPI>
 hipError_t gemm_tile_launch(const GemmArgs &a, int tiles16, hipStream_t st) {
   GemmArgs g = a;
   const int rows_per_group = EPI == EPI_SWIGLU ? WR * RTW / 2 : WR * RTW;
   g.n_groups = (tiles16 + rows_per_group - 1) / rows_per_group;
   g.n_colg = (a.ncols + 16 * WC * CTW - 1) / (16 * WC * CTW);
   const int blocks = g.n_colg > 1 ? (g.n_groups + 7) / 8 * 8 * g.n_colg : g.n_groups;
-  HS_LAUNCH((k_gemm_tile<DT, RTW, CTW, WR, WC, EPI>), dim3(blocks), dim3(64 * WR * WC), 0, st, g);
+  HS_LAUNCH((k_gemm_tile<RTW, CTW, WR, WC, EPI>), dim3(blocks), dim3(64 * WR * WC), 0, st, g);
   return hipGetLastError();
 }
 
@@ -1122,15 +1120,15 @@ hipError_t split_finish(const GemmArgs &g, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int DT, int EPI, int RTG, int CTG>
+template <int EPI, int RTG, int CTG>
 hipError_t gemm_lds_launch(const GemmArgs &a, int tiles16, int k_split, hipStream_t st) {
   GemmArgs g = a;
   g.k_split = k_split;
   const int blocks = lds_groups<EPI, RTG, CTG>(a, tiles16, k_split, g.n_groups, g.n_colg);
-  HS_LAUNCH((k_gemm_lds<DT, EPI, RTG, CTG>), dim3(blocks), dim3(64 * LG_NW), 0, st, g);
+  HS_LAUNCH((k_gemm_lds<EPI, RTG, CTG>), dim3(blocks), dim3(64 * LG_NW), 0, st, g);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || k_split <= 1) return e;
-  return split_finish<DT, EPI>(g, st);
+  return split_finish<HS_F32, EPI>(g, st);
 }
 
 // Many columns.  Where the work-group tile of 16 x 8 row x column tiles (wave
@@ -1149,16 +1147,16 @@ hipError_t gemm_lds_launch(const GemmArgs &a, int tiles16, int k_split, hipStrea
 // whose smaller work groups spread narrow matrices over more CUs (measured
 // crossover: between 64 and 80 work groups of the LDS kernel).
 constexpr int LDS_MIN_GROUPS = 72, LDS_BIG_GROUPS = 200, SPLITK_BELOW = 128, SPLITK_TARGET = 256, WIDE_COLS = 2048;
-template <int DT, int EPI>
+template <int EPI>
 hipError_t gemm_tiled(const GemmArgs &p, int tiles16, hipStream_t st) {
   int ng, nc;
   if (p.ncols >= WIDE_COLS && lds_groups<EPI, 16, 16>(p, tiles16, 1, ng, nc) >= LDS_BIG_GROUPS)
-    return gemm_lds_launch<DT, EPI, 16, 16>(p, tiles16, 1, st);
+    return gemm_lds_launch<EPI, 16, 16>(p, tiles16, 1, st);
   if (lds_groups<EPI, 16, 8>(p, tiles16, 1, ng, nc) >= LDS_BIG_GROUPS)
-    return gemm_lds_launch<DT, EPI, 16, 8>(p, tiles16, 1, st);
+    return gemm_lds_launch<EPI, 16, 8>(p, tiles16, 1, st);
   const int blocks = lds_groups<EPI, 8, 8>(p, tiles16, 1, ng, nc);
-  if constexpr (EPI == EPI_RESID || epi_qkv(EPI)) {
-    const int nkb = (p.K / Ty<DT>::CE + 15) / 16;
+  if constexpr (EPI == EPI_RESID || EPI == EPI_QKV) {
+    const int nkb = (p.K / Ty<HS_F32>::CE + 15) / 16;
     int ks = blocks < SPLITK_BELOW ? std::min(std::min(SPLITK_MAX, (SPLITK_TARGET + blocks - 1) / blocks), nkb / 4) : 1;
     if (ks > 1) {
       const int per = (nkb + ks - 1) / ks;
@@ -1166,12 +1164,12 @@ hipError_t gemm_tiled(const GemmArgs &p, int tiles16, hipStream_t st) {
     }
     const int prows = split_rows(p, EPI);
     if (ks > 1 && p.splitk_ws && prows % 4 == 0 && (int64_t)ks * p.ncols * prows <= p.splitk_cap)
-      return gemm_lds_launch<DT, EPI, 8, 8>(p, tiles16, ks, st);
+      return gemm_lds_launch<EPI, 8, 8>(p, tiles16, ks, st);
   }
-  if (blocks >= LDS_MIN_GROUPS) return gemm_lds_launch<DT, EPI, 8, 8>(p, tiles16, 1, st);
-  if constexpr (EPI == EPI_SWIGLU) return gemm_tile_launch<DT, 4, 4, 2, 2, EPI>(p, tiles16, st);
-  else if constexpr (EPI == EPI_RESID) return gemm_tile_launch<DT, 2, 2, 1, 4, EPI>(p, tiles16, st);
-  else return gemm_tile_launch<DT, 2, 4, 2, 2, EPI>(p, tiles16, st);
+  if (blocks >= LDS_MIN_GROUPS) return gemm_lds_launch<EPI, 8, 8>(p, tiles16, 1, st);
+  if constexpr (EPI == EPI_SWIGLU) return gemm_tile_launch<4, 4, 2, 2, EPI>(p, tiles16, st);
+  else if constexpr (EPI == EPI_RESID) return gemm_tile_launch<2, 2, 1, 4, EPI>(p, tiles16, st);
+  else return gemm_tile_launch<2, 4, 2, 2, EPI>(p, tiles16, st);
 }
 
 // A residual projection that leaves its sum to the next RMSNorm
@@ -1235,7 +1233,7 @@ hipError_t gemm_shape(const GemmArgs &a, hipStream_t st) {
   if (tiles <= 1) return gemm_global_r<DT, EPI, 1>(p, tiles16, st);
   if (tiles <= 2) return gemm_global_r<DT, EPI, 2>(p, tiles16, st);
   if constexpr (DT == HS_F32) {
-    return gemm_tiled<DT, EPI>(p, tiles16, st);
+    return gemm_tiled<EPI>(p, tiles16, st);
   } else {
     int parts = 0;
     const hipError_t e = gemm_dma<DT>(EPI, p, tiles16, &parts, st);

@@ -68,4 +68,6 @@ SHAPE_CASES = {
 
 
 def shape_cfg(model: str) -> dict:
+    if model == "f32":  # (fp32 storage runs other GEMMs; see test_gpu_gemm_shapes.py)
+        return dict(configs.get("tiny", n_layers=1), d_model=1024, n_heads=16, n_kv_heads=16, ffn_dim=5504, vocab=8192)
     return configs.get(model, n_layers=1)
