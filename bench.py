@@ -530,8 +530,8 @@ def run_workload(name: str, args, ws_cache: dict, stream_gbs: float, headline: b
 KERNEL_LEGEND = """Template arguments. `k_gemm<dtype, row tiles, column tiles, waves, k-blocks per group, prologue, LDS
 staging, epilogue, packed SwiGLU output, packed activations>` (columns <= 32); `k_gemm_dma<dtype, wave rows, wave
 columns, row tiles/wave, column tiles/wave, sub-blocks per stage, stages, epilogue, streamed weights>` (16-bit, more
-columns); `k_gemm_lds<dtype, epilogue, row tiles, column tiles>` and `k_gemm_tile<dtype, row tiles/wave, column
-tiles/wave, wave rows, wave columns, epilogue>` (fp32, more columns);
+columns); `k_gemm_lds<epilogue, row tiles, column tiles>` and `k_gemm_tile<row tiles/wave, column tiles/wave,
+wave rows, wave columns, epilogue>` (fp32, more columns);
 `k_attn<dtype, head_dim, group, waves, paged cache>` (scalar split attention), `k_attn_mma<...>` (GQA on the matrix
 cores), `k_attn_prefill<dtype, head_dim, group, waves, query tiles/wave>` (causal prefill); `k_combine<dtype, head_dim, splits unrolled>`. dtype 1 = f16,
 2 = bf16; prologue 0 = plain activations, 1 = RMSNorm, 2 = attention split combine; epilogue 0 = logits,

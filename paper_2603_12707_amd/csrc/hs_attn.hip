@@ -24,7 +24,7 @@ __device__ __forceinline__ float merge_weight(float m_part, float m_all) {
 }
 
 // element (row, c) of the combined output: rows of n_heads * head_dim, or the
-// packed activation layout the O projection reads at 2..32 columns
+// packed activation layout where the O projection reads it (gemm_x_packed)
 __device__ __forceinline__ int64_t attn_out_at(const AttnArgs &a, int64_t row, int c, int hd) {
   const int K = a.n_heads * hd;
   return a.out_packed ? packed_x_index((int)row, c, (K / 8 + 15) / 16) : row * K + c;
@@ -487,7 +487,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 // tiles together make the k range of one 16x16x32 MFMA.
 //
 // What bounds it: the softmax arithmetic (about 12 vector instructions a
-// score) and the PV products (the parts double or triple them) in turn.
+// score) and the products (the parts double or triple those of PV) in turn:
+// over sixteen requests (bf16, group 7, 14370 rows, 274-283 us) the vector
+// units are busy half of the time and the matrix cores 43 %, LDS 11 % without
+// bank conflicts.  One request of 640 rows (25-26 us, 320 work groups) is a
+// chain of its longest groups' steps, the matrix cores 7 % busy.
 //
 // Slack, in units of the base-2 exponent, by which a column's scores may pass
 // the running maximum before it is raised: exp2(s - m) stays below 2^11.5.

@@ -1131,21 +1131,23 @@ hipError_t gemm_lds_launch(const GemmArgs &a, int tiles16, int k_split, hipStrea
   return split_finish<HS_F32, EPI>(g, st);
 }
 
-// Many columns.  Where the work-group tile of 16 x 8 row x column tiles (wave
-// tiles of 4 x 4, half the LDS reads per MFMA) still gives LDS_BIG_GROUPS
-// work groups, it is taken (prefill gate/up at 640 rows: 159 against 191 us;
-// with the threshold at 200 instead of 384 the 640-row q/k/v takes it too,
-// and the LLaVA-shaped prefill went from 21.1 to 20.2 ms).  From
-// WIDE_COLS columns on, 16 x 16 tiles (wave tiles of 4 x 8: 0.375 KB of LDS
-// reads per MFMA instead of 0.5; 128 KB of LDS) where they give as many work
-// groups; below that the 256-column groups pad too much (gate/up at 640
-// rows: 240 against 172 us).
-// A GEMM (residual or q/k/v) with fewer than SPLITK_BELOW work groups
-// splits K (up to SPLITK_MAX ways, at least 4 k-blocks each) when the
-// partials fit the workspace.  Otherwise the LDS-staged kernel from
-// LDS_MIN_GROUPS work groups up, and below that the register-tiled kernel,
-// whose smaller work groups spread narrow matrices over more CUs (measured
-// crossover: between 64 and 80 work groups of the LDS kernel).
+// Many columns in fp32 storage.  Work-group tiles of 16 x 8 row x column tiles
+// (wave tiles of 4 x 4, half the LDS reads per MFMA of 8 x 8) where they give
+// LDS_BIG_GROUPS work groups; from WIDE_COLS columns on 16 x 16 where these
+// give as many.  A GEMM (residual or q/k/v) with fewer than SPLITK_BELOW work
+// groups splits K (up to SPLITK_MAX ways, at least 4 k-blocks each) when the
+// partials fit the workspace.  Otherwise 8 x 8 from LDS_MIN_GROUPS work groups
+// up, and below that the register-tiled kernel, whose smaller work groups
+// spread narrow matrices over more CUs.
+// The lines were drawn on 16-bit storage, which runs k_gemm_dma instead.  In
+// fp32, whose MFMAs take several times as long, the choice against the best
+// tile and split tried (LLaVA-shaped layer, us): up to 256 columns gate/up, O,
+// down and the head are within 3 %, q/k/v is not (33 columns: three splits, 181
+// against 135 in two; 256: none, 267 against 236 in four); above, the larger tiles and unsplit projections leave too few work groups a
+// round: over 400 columns O 257 against 148 (two splits), down 681 against 361
+// (two), gate/up 992 against 754 (8 x 8), over 2100 down 2678 against 1625
+// (three splits), gate/up 3953 against 2982 (16 x 8), the head 4955 against
+// 4280 (8 x 8); over 640 gate/up and q/k/v run the best.
 constexpr int LDS_MIN_GROUPS = 72, LDS_BIG_GROUPS = 200, SPLITK_BELOW = 128, SPLITK_TARGET = 256, WIDE_COLS = 2048;
 template <int EPI>
 hipError_t gemm_tiled(const GemmArgs &p, int tiles16, hipStream_t st) {
@@ -1274,7 +1276,7 @@ bool gemm_x_packed(int dtype, int ncols, int K) {
 }
 
 int resid_defer_splits(int dtype, int ncols, int K, int d_model, int64_t cap) {
-  // the projection reads its activations from memory (k_gemm over 2..32
+  // the projection reads its activations from memory through k_gemm (up to 32
   // columns), the next normalisation runs in k_rmsnorm (its columns do not
   // fit the prologue's LDS copy), every split holds a k-block, whole float4
   // rows, and the fp64 partials fit the workspace

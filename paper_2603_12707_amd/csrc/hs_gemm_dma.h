@@ -12,40 +12,6 @@
 namespace hs {
 namespace dev {
 
-// Y[c][n] = sum_k X[c][k] W[n][k].  Weights and activations sit in the packed
-// layout (16 rows or columns x 32 elements = 1 KB in MFMA operand order), so
-// one wave-wide 16-byte buffer load to LDS moves one sub-block, lane l's 16
-// bytes to LDS byte 16 l, and a wave reads an MFMA operand back with one
-// conflict-free ds_read_b128.  No register and no write instruction stages the
-// data.
-//
-// A work group of WR x WC waves owns TR = WR RTW row tiles and TC = WC CTW
-// column tiles; wave (wr, wc) computes RTW x CTW of them over the work group's
-// K range.  K advances in stages of KS sub-blocks through a ring of ST stages
-// in LDS.  A wave reads the operands of the next sub-block while it issues the
-// MFMAs of the present one, the reads spread between them.  At a stage's last
-// sub-block it waits for its own loads of the next stage (the counter then
-// still covers ST - 2 stages), meets the others at one barrier, and requests
-// the stage ST on into the slot that this one leaves (its operands are in
-// registers by then).
-//
-// The shapes of decode batches take two sub-blocks per stage: half the
-// barriers, and 2 KB of a row tile requested at a time; where a single column
-// group reads the weights, they are loaded with the non-temporal hint.  Decode
-// layer: 120 requests 297 -> 277 us, 75 326 -> 314, 256 623 -> 610; gate/up
-// over 75 columns (22016 x 4096) 52.9 -> 42.9 us, over 120 (37888 x 3584)
-// 60.7 -> 54.7, over 256 85.6 -> 80.2.  The loads alone, in this order without
-// the arithmetic, take 35-37 and 48 us there.
-//
-// What bounds it.  In decode about 36-40 B/ns of operands pass per CU: weights
-// from HBM (6.1 TB/s, 24 B/ns per CU, is all that loads alone reach) and
-// activations from L2 together (those alone reach 128 B/ns), so a tile's time
-// is about its bytes, 1 KB x (TR + TC) per sub-block, and the launcher takes
-// the shape with the fewest bytes per CU that still fills the chip.  At the largest tile (16 x 16) that is as long as the power limit
-// leaves the matrix cores (1.9 GHz, MFMA 65 % busy): 37888 x 3584 over 14400
-// columns runs 2.81-3.06 ms, 1250-1390 TFLOP/s; with both operands staged
-// through registers it took 4.05 ms.  A 4-wave variant with wave tiles of
-// 8 x 8 (one wave per SIMD, a quarter fewer LDS reads) took 3.82 ms.
 // NR LDS reads spread over NM MFMAs
 template <int I, int NR, int NM>
 __device__ __forceinline__ void dma_sched() {
@@ -246,6 +212,47 @@ __device__ __forceinline__ void dma_qkv(const GemmArgs &a, unsigned char *s_mem,
   }
 }
 
+// Y[c][n] = sum_k X[c][k] W[n][k].  Weights and activations sit in the packed
+// layout (16 rows or columns x 32 elements = 1 KB in MFMA operand order), so
+// one wave-wide 16-byte buffer load to LDS moves one sub-block, lane l's 16
+// bytes to LDS byte 16 l, and a wave reads an MFMA operand back with one
+// conflict-free ds_read_b128.  No register and no write instruction stages the
+// data.
+//
+// A work group of WR x WC waves owns TR = WR RTW row tiles and TC = WC CTW
+// column tiles; wave (wr, wc) computes RTW x CTW of them over the work group's
+// K range.  K advances in stages of KS sub-blocks through a ring of ST stages
+// in LDS.  A wave reads the operands of the next sub-block while it issues the
+// MFMAs of the present one, the reads spread between them.  At a stage's last
+// sub-block it waits for its own loads of the next stage (the counter then
+// still covers ST - 2 stages), meets the others at one barrier, and requests
+// the stage ST on into the slot that this one leaves (its operands are in
+// registers by then).
+//
+// The shapes of decode batches take two sub-blocks per stage: half the
+// barriers, and 2 KB of a row tile requested at a time; where a single column
+// group reads the weights, they are loaded with the non-temporal hint.  Decode
+// layer: 120 requests 297 -> 277 us, 75 326 -> 314, 256 623 -> 610; gate/up
+// over 75 columns (22016 x 4096) 52.9 -> 42.9 us (traced alone 44.8), over 120
+// (37888 x 3584) 60.7 -> 54.7 (57.1), over 256 85.6 -> 80.2 (81.4).  The loads
+// alone, in this order without the arithmetic, take 35-37 us over 75 columns
+// and 48 over 120.
+//
+// What bounds it.  In decode about 36-40 B/ns of operands pass per CU: weights
+// from HBM (in this order loads alone reach 6.1 TB/s, 24 B/ns per CU; a plain
+// read of 4 GiB reaches 7.0) and activations from L2 (loads alone 128 B/ns)
+// together, so a tile's time is about its bytes, 1 KB x (TR + TC) per
+// sub-block, and the launcher takes the shape with the fewest bytes per CU that
+// still fills the chip.  The largest tile (16 x 16) is bound by the clock that
+// the power limit leaves and by the waits at its stages: 37888 x 3584 over
+// 14370 columns runs 3.0-3.2 ms (1220-1310 TFLOP/s; hipBLASLt 3.15), at
+// 1.85 GHz, its MFMAs 64 % busy, its waves waiting 28 % of their time, LDS 24 %
+// busy without bank conflicts; with both operands staged through registers it
+// took 4.05 ms.  A 4-wave variant with wave tiles of 8 x 8 (one wave per SIMD,
+// a quarter fewer LDS reads) took 3.82 ms.  One round of 230-240 work groups
+// (640 rows) keeps its MFMAs 35-50 % busy: each group fills its ring, runs and
+// stores with nothing beside it.
+//
 // EPI: EPI_SWIGLU; EPI_QKV (bias, RoPE, R(q), K/V append; K not split); or
 // EPI_STORE, fp32 rows by a.f32_out: logits, K-split partials (residual rows,
 // or q|k|v rows in turn), or the residual add

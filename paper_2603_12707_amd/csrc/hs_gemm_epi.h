@@ -50,8 +50,9 @@ __device__ __forceinline__ void tile_map(const GemmArgs &a, int g, int *mat, int
 }
 
 // PK: the SwiGLU output goes to the packed activation layout where a.out_packed
-// says so (the down projection reads it so, which happens at 2..32 columns,
-// the widths k_gemm serves; the kernels for wider GEMMs never write it)
+// says so (the down projection reads it so): k_gemm's, up to 32 columns.
+// k_gemm_dma stores that layout in its own epilogue, and the fp32 kernels for
+// wider GEMMs never write it.
 template <int DT, int EPI, int R, bool PK = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const int *mat, const int *row0, const f32x4 *v,
                                               int col, int rr) {

@@ -51,8 +51,14 @@ struct DmaPlan {
 // idle or more, is cut over K instead into as many ranges as give every CU one:
 // 3584 x 18944 over 14370 columns, 798 tiles of 16 x 16, takes three rounds and
 // an eighth instead of four (O and down, both layers: 4270 -> 3770 us).
-// Measured against the estimate at 64..640 columns of both 7B-shaped
-// models: the chosen shape is within 6 % of the best one.
+// How far the choice is from the best: every shape and split timed for each
+// GEMM of both 7B-shaped models at 33, 48, 64, 75, 96, 120, 160, 200, 256, 320,
+// 512 and 640 columns, weights from HBM.  Of the 120, 93 are within 6 % of the
+// best and 113 within 15 %, 3 % in the sum.  The worst are O over 75-120
+// columns (4096 x 4096 over 120: 22.0 us with 8 splits of 8 x 8 tiles, 17.0 with
+// 4 of 8 x 4) and down over 320 (52.6 against 44.3; 74.9 against 63.4); q/k/v is
+// up to 14 % off, the LM head 13 %, gate/up 5 %.  (O and q/k/v of 64-160 columns
+// would do with half the splits.)
 inline bool dma_plan(int epi, const GemmArgs &a, int tiles16, DmaPlan *best) {
   static constexpr DmaShape shapes[] = {
 #define HS_DMA_ENTRY(I, WR, WC, RTW, CTW, KS, ST) {WR * RTW, WC * CTW, KS * ST},

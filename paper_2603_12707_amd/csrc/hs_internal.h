@@ -12,9 +12,6 @@
 
 namespace hs {
 
-// Arguments of the weight-streaming GEMM  Y[c][n] = sum_k X[c][k] * W[n][k].
-// Columns c are activation rows (decode requests or prefill rows); rows n are
-// output features.  Row tiles of 16 are enumerated over up to three matrices.
 // The rows of one prefill pass: up to PACK_MAX requests, their rows packed
 // request by request.  Request i of the pass is KV request req[i] and owns the
 // rows cu[i] .. cu[i + 1] - 1, its positions 0 .. cu[i + 1] - cu[i] - 1.
@@ -53,6 +50,9 @@ struct KvRef {
   int paged;       // 0: one block per request (toff[r] = r, bt = cap, act[c] = c)
 };
 
+// Arguments of the weight-streaming GEMM  Y[c][n] = sum_k X[c][k] * W[n][k].
+// Columns c are activation rows (decode requests or prefill rows); rows n are
+// output features.  Row tiles of 16 are enumerated over up to three matrices.
 struct GemmArgs {
   const void *w[3];
   const void *bias[3];
@@ -211,8 +211,8 @@ struct AttnArgs {
 
 hipError_t launch_gemm(int dtype, int pro, int epi, const GemmArgs &a, hipStream_t st);
 // whether a GEMM over ncols columns with K-long 16-bit activations reads them
-// from memory through MFMA-operand loads (2..32 columns that the LDS copy
-// cannot hold); its producer then writes them in the packed activation layout
+// from memory in MFMA operand order (whatever one column tile's LDS copy cannot
+// hold); its producer then writes them in the packed activation layout
 bool gemm_x_packed(int dtype, int ncols, int K);
 // K splits a residual projection over K inputs leaves pending for the next
 // RMSNorm over d_model (0: it adds into the residual rows itself); cap is
@@ -229,17 +229,17 @@ hipError_t launch_pack(int dtype, const void *src, int64_t rows, int64_t cols, v
 int64_t packed_elems(int dtype, int64_t rows, int64_t cols);
 hipError_t launch_attention(int dtype, int head_dim, int group, int nq, const AttnArgs &a, hipStream_t st);
 hipError_t launch_combine(int dtype, int head_dim, int nq, const AttnArgs &a, hipStream_t st);
-// causal prefill attention over the packed rows of *a.pk (nrows in all), 16-bit storage; query
-// tiles of 16 / group rows
-// causal prefill attention in work groups of PREFILL_WAVES waves: fills
-// groups[0..n) (each request's work groups per KV head) for the packed rows
-// cu[0..n]; returns the query tiles per wave
+// causal prefill attention (16-bit storage) in query tiles of 16 / group rows
+// and work groups of PREFILL_WAVES waves: fills groups[0..n) (each request's
+// work groups per KV head) for the packed rows cu[0..n]; returns the query
+// tiles per wave
 constexpr int PREFILL_WAVES = 4;
 int attn_prefill_groups(int group, int n_kv, int n, const int *cu, int *groups);
 // most work groups per KV head of a pass of `rows` rows (a group covers at
 // least 8 rows of one request)
 inline int64_t prefill_groups_max(int64_t rows) { return rows / 8 + PACK_MAX; }
 bool attn_prefill_on_mma(int dtype);
+// over the packed rows of *a.pk, nrows in all
 hipError_t launch_attention_prefill(int dtype, int head_dim, int group, int nrows, const AttnArgs &a,
                                     hipStream_t st);
 // x[c] = E[tokens[act[c]]] (act NULL: tokens[c])

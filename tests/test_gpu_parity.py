@@ -257,11 +257,10 @@ def test_many_columns_split_k_qkv():
 
 @pytest.mark.parametrize("d_model,n_heads,n_kv_heads,qkv_bias,dtype", [(1024, 8, 2, 1, "bf16"), (512, 4, 4, 0, "f16")])
 def test_weight_stationary_columns(d_model, n_heads, n_kv_heads, qkv_bias, dtype):
-    """150 requests (129..256 columns): gate/up and the LM head take the
-    weight-stationary GEMM (two column groups, the second ragged; F = 1000
-    leaves a ragged last gate/up task and V = 997 a ragged LM head), while
-    q/k/v, O and down stay on the LDS-staged kernel (at d = 1024 with K
-    split two ways)."""
+    """150 requests, two decode steps: three column groups of 64 columns, the
+    last one ragged (F = 1000 leaves a ragged last gate/up row group and V = 997
+    a ragged LM head), q/k/v and down with K split (four ways at d = 1024), O
+    with (d = 1024) and without."""
     cfg = small_cfg(n_layers=1, d_model=d_model, n_heads=n_heads, n_kv_heads=n_kv_heads, head_dim=128, ffn_dim=1000,
                     dtype=dtype, qkv_bias=qkv_bias)
     n_v = [(13 * b) % 11 for b in range(150)]
@@ -412,7 +411,7 @@ def test_decode_step_replays_from_a_hip_graph(case):
     sampled requests agree with the oracle fed the same tokens; eager work and
     synchronisation run between the replays.  Cases: 3 requests (activations
     staged in LDS), 20 requests at d = 1024 (packed activations read from
-    memory), 150 requests (the weight-stationary gate/up and LM head)."""
+    memory), 150 requests (the many-column GEMM, with and without K splits)."""
     import paper_2603_12707_amd as hs
     if case == "three":
         cfg = small_cfg(dtype="bf16", n_heads=8, n_kv_heads=2, head_dim=64)
@@ -499,7 +498,7 @@ def test_repeat_runs_are_bit_identical(case):
     """Determinism: the same prefills and decode steps on two fresh caches give
     bit-identical tokens, logits and K/V rows (no floating-point atomics; every
     reduction in a fixed order): one request long enough for split attention
-    merged in the O projection's prologue, and 40 requests (K-split LDS GEMMs,
+    merged in the O projection's prologue, and 40 requests (K-split GEMMs,
     split attention and the combine kernel)."""
     import paper_2603_12707_amd as hs
     if case == "b1_splits":

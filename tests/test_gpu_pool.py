@@ -115,8 +115,8 @@ def test_pool_parity_across_blocks_and_continuous_batching():
 
 def test_pool_packed_activations_and_wide_prefill():
     """20 requests in 22 slots at d = 1024 (GQA-4 with bias, F = 1000): one
-    prefill call packs their ~150 rows (gate/up and the LM head on the
-    weight-stationary kernel), and the 20-column decode steps read packed
+    prefill call packs their ~150 rows (the many-column GEMM, its q/k/v partials
+    finished into the blocks), and the 20-column decode steps read packed
     activations while the q/k/v epilogue appends into the blocks."""
     cfg = small_cfg(n_layers=1, d_model=1024, n_heads=8, n_kv_heads=2, head_dim=128, ffn_dim=1000, dtype="bf16",
                     qkv_bias=1)

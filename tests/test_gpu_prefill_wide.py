@@ -4,13 +4,15 @@ depend on the whole of layer 0.
 Two 2-layer models (d = 1024, d_h = 128, F = 2048; fp16 MHA with 1-D RoPE, and
 bf16 GQA-7 with 3-section M-RoPE and q/k/v bias) are prefilled
   * one request of 640 rows alone: causal matrix-core prefill attention at 640
-    rows, the 8 x 8-tile LDS GEMM for gate/up, K splits for q/k/v, O and down;
-  * two requests of 1024 rows packed into one 2048-row pass: the 16 x 8-tile
-    LDS GEMM for q/k/v and gate/up, the unsplit 8 x 8-tile one for O and down;
-  * four such requests packed into one 4096-row pass: the 16 x 16-tile LDS GEMM
-    for q/k/v and gate/up, the 16 x 8-tile one for O and down.
-(The tile choice follows the work-group counts of the GEMM launcher's rule at
-these shapes.)  Each request's first token and last-row logits, and its
+    rows, the many-column GEMM's small tiles (6 x 8 gate/up), K splits for q/k/v
+    and down (and O of the GQA model);
+  * two requests of 1024 rows packed into one 2048-row pass: 16 x 8 tiles with
+    the q/k/v epilogue of their own, 8 x 16 for gate/up, 8 x 4 added straight
+    into the residual for O and down;
+  * four such requests packed into one 4096-row pass: 12 x 20 (MHA) and 8 x 20
+    (GQA) tiles for q/k/v, 16 x 16 for gate/up, 8 x 8 for O and down.
+(Row x column tiles of 16, as the GEMM's launch rule chooses them at these
+sizes.)  Each request's first token and last-row logits, and its
 layer-1 K/V rows at sampled positions, are compared with the oracle's values
 in tests/golden/prefill_wide.json, written by make_prefill_golden.py from the
 oracle alone.  Layer-1 rows are projections of the residual stream after
