@@ -158,15 +158,16 @@ inline StepScratch step_scratch(const hs_config &c, int64_t n, int n_split) {
 }
 // Floats of K-split partials that decode steps over n columns split by, the
 // same in the model's workspace and in the static array, so that both run the
-// same kernels: what splitk_floats_for asks for, or SPLITK_MAX splits of the
-// widest GEMM where the static array holds only those beside the layers'
-// scratch (the logits take the layers' place).
+// same kernels: what splitk_floats_for asks for, or where the static array
+// takes the step (SPLITK_MAX splits of the widest GEMM beside the layers'
+// scratch) but not with all of them, as many as it holds there (the logits
+// take the layers' place).
 inline int64_t step_splitk_floats(const hs_config &c, int64_t n, int n_split) {
   const int64_t rows = splitk_rows(c), all = splitk_floats_for(n, n, rows), few = (int64_t)SPLITK_MAX * n * rows;
   const uint64_t layers = step_scratch(c, n, n_split).layers();
-  const bool only_few = layers + whole256(all * 4) > HS_STATIC_SCRATCH_BYTES &&
-                        layers + whole256(few * 4) <= HS_STATIC_SCRATCH_BYTES;
-  return only_few ? few : all;
+  if (layers + whole256(few * 4) > HS_STATIC_SCRATCH_BYTES) return all;
+  const int64_t room = (int64_t)((HS_STATIC_SCRATCH_BYTES - layers) / 256 * 64);
+  return all < room ? all : room;
 }
 // the attention combine runs in the projection's prologue for at most this
 // many splits (and activations that fit the prologue's LDS copy)

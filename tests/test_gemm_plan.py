@@ -74,7 +74,7 @@ def test_step_scratch_of_all_sizes(lib):
     step, they hold SPLITK_MAX splits of the widest GEMM, and the q/k/v, O and down plans find room."""
     import ctypes
     r = random.Random(3)
-    static, few_seen = 64 << 20, 0
+    static, less_seen = 64 << 20, 0
     for _ in range(4000):
         hd, nkv, g = r.choice([64, 128]), r.choice([1, 2, 4, 8, 32]), r.choice([1, 2, 4, 7, 8])
         d, F = 8 * r.randint(1, 700), 8 * r.randint(1, 2500)
@@ -88,8 +88,8 @@ def test_step_scratch_of_all_sizes(lib):
         assert floats <= max(4 * n * rows, min(8 * n * rows, 16 << 20)), what
         if layers + few <= static:  # accepted, with the caller's logits or (logits in the layers' place) its own
             assert layers + -(-4 * floats // 256) * 256 <= static, what
-        few_seen += floats < min(8 * n * rows, 16 << 20)
-    assert few_seen > 50
+        less_seen += floats < min(8 * n * rows, 16 << 20)
+    assert less_seen > 50
 
 
 def test_shape_cases_run_every_kind(lib):
