@@ -603,7 +603,7 @@ def summarise_stats(trace_dir: str, bench_log: str, workload: str, command: str)
     rl = res["roofline"]
     md = f"""# Decode, `{workload}` — rocprofv3 kernel statistics
 
-Command (GPU box, repository root), then `python bench.py --summarise-stats` on its output:
+Command (repository root), then `python bench.py --summarise-stats` on its output:
 
 ```
 {command}
@@ -674,7 +674,7 @@ def summarise_counters(fetch_dir: str, write_dir: str, workload: str, kind: str,
 kernel: `{kernel}`
 kernel_source_sha256: {kernel_source_hash(kind)}
 
-Commands (GPU machine, repository root), one counter per run, then `python bench.py --summarise-counters` on their
+Commands (repository root), one counter per run, then `python bench.py --summarise-counters` on their
 output:
 
 ```
